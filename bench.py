@@ -10,10 +10,9 @@ FP64-arithmetic (stochastic rounding) forms, and the FP32 form with the
 Eq. 52 correlation and the Sec. 3.2 correction term, are timed on the same
 lattice and reported under "variants".
 
-A step is one time step of all three lattices over the whole lattice.  The
-FP32 forms advance two steps per launch (an odd last step of a call
-alone; the call's last launch also writes the macroscopic fields); the
-other forms one.  Inputs are
+A step is one time step of all three lattices over the whole lattice.  Every
+form advances two steps per launch (an odd last step of a call alone; the
+call's last launch also writes the macroscopic fields).  Inputs are
 resident in device memory before timing starts.  The time of K steps (one
 call) is taken with HIP events on the stream the library queues on, between
 two device synchronisations.
@@ -59,6 +58,8 @@ FORM_ARITHMETIC = {
 # the correction term of Sec. 3.2 -- at no extra memory traffic.
 EXTRA = {"f32ext": dict(thermal_correction=1, pore_size=0.0135)}
 KERNEL_SOURCES = ["paper_1608_04118_amd/csrc/step_kernel.hpp", "paper_1608_04118_amd/csrc/step2_kernel.hpp",
+                  "paper_1608_04118_amd/csrc/tile_kernel.hpp", "paper_1608_04118_amd/csrc/tile_launch.hpp",
+                  "paper_1608_04118_amd/csrc/tile.hip", "paper_1608_04118_amd/csrc/tile_shapes.hip",
                   "paper_1608_04118_amd/csrc/common.hpp",
                   "paper_1608_04118_amd/csrc/host_common.hpp", "paper_1608_04118_amd/csrc/lbm_ltne.hip",
                   "paper_1608_04118_amd/build.py"]
@@ -117,7 +118,7 @@ VALU_ISSUE_PER_S = CUS * CLOCK_HZ
 
 # Forms whose steps run two to a launch on the 8192^2 layer (an odd last step
 # of a call alone)
-TWO_STEP = ("f32", "f32ext", "f64")
+TWO_STEP = ("f32", "f32ext", "f64", "f16s", "f32sr")
 
 
 def _events_ms(stream, fn):
@@ -277,15 +278,21 @@ def copy_bandwidth(gib: float = 1.0, reps: int = 5):
     return {"bytes_read": n * 4, "bytes_written": n * 4, "ms": ms, "gbs": 2 * n * 4 / ms / 1e6}
 
 
-# element type of each two-step form's kernel, as rocprofv3 names it
-TWO_STEP_TYPE = {"f32": "float", "f64": "double"}
+# storage and arithmetic type of each two-step form's kernel, as rocprofv3
+# names them (demangled, mangled)
+TWO_STEP_TYPE = {"f32": ("float, float", "ff"), "f64": ("double, double", "dd"), "f16s": ("_Float16, float", "DF16_f"),
+                 "f32sr": ("float, double", "fd")}
 
 
 def is_two_step_kernel(name: str, tag: str = "f32") -> bool:
     """The two-step kernel of form `tag` with the porosity field (the 8192^2
-    layer's), by its demangled or mangled name in a rocprofv3 record."""
-    t = TWO_STEP_TYPE[tag]
-    return ("step2_kernel<%s, 1>" % t) in name or ("step2_kernelI%sLi1E" % t[0]) in name
+    layer's), by its demangled or mangled name in a rocprofv3 record (older
+    records name the kernel step2_kernel, by the storage type alone)."""
+    t, m = TWO_STEP_TYPE[tag]
+    if ("tile2_kernel<%s, 1>" % t) in name or ("tile2_kernelI%sLi1E" % m) in name:
+        return True
+    return tag in ("f32", "f64") and (("step2_kernel<%s, 1>" % t.split(",")[0]) in name or
+                                      ("step2_kernelI%sLi1E" % m[0]) in name)
 
 
 def _merge_record(out_path: str, tag: str, rec: dict):
@@ -561,7 +568,7 @@ def roofline(head: str, r: dict, traffic):
            "bytes_per_launch": must, "launch_ms": round(r["launch_ms"], 4)}
     if r["steps_per_launch"] == 2:
         eq = must * 2 / launch_s / 1e9
-        out["kernel"] = ("step2_kernel<float, kPhiField>: two time steps per launch over %d^2 nodes; %d B per node "
+        out["kernel"] = ("tile2_kernel<float, float, kPhiField>: two time steps per launch over %d^2 nodes; %d B per node "
                          "per launch (state read and written once)" % (N, BYTES_PER_LUP[head]))
         out["one_step_equivalent"] = {"bytes_per_launch": must * 2, "gbs": round(eq, 1),
                                       "frac": round(eq / HBM_PEAK_GBS, 4)}

@@ -179,15 +179,12 @@ int lbm_ltne_create(const lbm_ltne_params *p, const double *phi_field, const dou
                     const double *Tf_init, const double *Ts_init, void *hip_stream,
                     void *device_pool, size_t pool_bytes, lbm_ltne_t *out);
 
-/* Advances nsteps >= 0 time steps (asynchronous).  Each step is one fused
- * launch: pull streaming, wall reconstruction, macros, the three collisions,
- * store.  In the FP32 and FP64 forms, on lattices that yield at least 1024
- * (FP32) or 2560 (FP64) strips of 62 (periodic x) or 61 columns by 8 rows,
- * the steps of a call advance in pairs, two steps per launch with the
- * intermediate time level kept on chip (an odd last step, and the steps
- * checked under diag_every, alone); the result equals single steps bit for
- * bit.  Small lattices run their steps in recorded sequences of launches (a
- * HIP graph).  The macros of the last step are kept for
+/* Advances nsteps >= 0 time steps (asynchronous).  A step is fused: pull
+ * streaming, wall reconstruction, macros, the three collisions, store.  The
+ * steps of a call advance in pairs, two steps per launch with the
+ * intermediate time level kept on chip (an odd last step, the steps checked
+ * under diag_every, and lattices with rows of 256 MB and more alone); the
+ * result equals single steps bit for bit.  The macros of the last step are kept for
  * lbm_ltne_macros, lbm_ltne_nusselt and lbm_ltne_diagnostics; the residual
  * compares them with the macros kept by the previous call that advanced the
  * lattice (a call with nsteps = 0 changes nothing).  With diag_every > 0 a
@@ -260,12 +257,12 @@ int lbm_ltne_destroy(lbm_ltne_t h);
 
 /*
  * Batched lattices: n independent lattices of uneven size and parameters
- * (one precision per batch) advanced together.  By default (mode 0) a batch
- * step is one launch over the combined tile list of all lattices (FP32
- * batches of at least 1024 strips of 8 rows: pairs of steps per launch, as in
- * lbm_ltne_step, with per-lattice chunk heights, 16 rows by default); mode 1
+ * (one precision per batch) advanced together.  By default (mode 0) a launch
+ * covers the combined tile list of all lattices and advances them by a pair
+ * of steps, as in lbm_ltne_step (an odd last step alone); mode 1
  * runs all steps of a call in one persistent cooperative launch with a
- * grid-wide barrier between steps (every barrier wait is bounded; a timeout
+ * grid-wide barrier between steps (between pairs of steps in FP32 batches of
+ * at least 1024 strips of 61 or 62 columns by 8 rows; every barrier wait is bounded; a timeout
  * is reported as LBM_EHIP by the next synchronizing call).  Every lattice
  * evolves exactly as a single lattice with the same parameters would.
  *   ps: n parameter sets (diag_every must be 0: LBM_EUNSUPPORTED otherwise);
@@ -290,15 +287,15 @@ int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t *nodes, int32_t *tiles, int3
 /* Tile width of each lattice as log2 (6, 7, 8 = 64, 128, 256 nodes wide; 0 = default). */
 int lbm_ltne_batch_set_tiles(lbm_ltne_batch_t b, const int32_t *tile_shift);
 int lbm_ltne_batch_get_tiles(lbm_ltne_batch_t b, int32_t *tile_shift);
-/* Chunk height (rows) of each lattice's wavefronts in the two-step launches
- * of an FP32 batch: 8, 12, 16, 24 or 32 (0 = default 16). */
+/* Chunk height (rows) of each lattice's wavefronts in the persistent launch
+ * of an FP32 batch that runs pairs of steps: 8, 12, 16, 24 or 32 (0 = default 16). */
 int lbm_ltne_batch_set_chunks(lbm_ltne_batch_t b, const int32_t *rows);
 int lbm_ltne_batch_get_chunks(lbm_ltne_batch_t b, int32_t *rows);
 /* Autotuner: for each size class (lattices of equal nx) tries tile widths
- * 64/128/256 by timing reps single-step launches, then (FP32 batches that
- * run two steps per launch) chunk heights 8..32 by timing 2 reps steps of
- * two-step launches, then the launch mode (one launch per step or pair of
- * steps, or one persistent launch; skipped when the device has no resident
+ * 64/128/256 by timing reps single-step launches, then (FP32 batches whose
+ * persistent launch runs pairs of steps) chunk heights 8..32 by timing 2 reps
+ * steps of that launch, then the launch mode (one launch per pair of steps,
+ * or one persistent launch; skipped when the device has no resident
  * grid for it) by timing 2 reps steps of each, every trial from a snapshot
  * of the state (restored afterwards), and keeps the fastest of each;
  * ms_per_step (may be NULL) receives the time per step of the chosen

@@ -2,6 +2,8 @@
 // parameters advanced together, either by one launch per step over the
 // combined tile list (the default), or by one persistent cooperative launch
 // that loops over the time steps with a grid-wide barrier between steps.
+// The ordinary launches advance two steps each over tiles held in LDS
+// (tile_kernel.hpp).
 // On MI355X the barrier's device-scope release and acquire (L2 write-back
 // and invalidation on every XCD, once per resident workgroup) cost more than
 // a kernel launch per step, so the per-step form is the default.  Every lattice keeps
@@ -20,30 +22,9 @@
 #include "reduce_kernels.hpp"
 #include "step2_kernel.hpp"
 #include "step_kernel.hpp"
+#include "tile_launch.hpp"
 
 namespace ltne {
-
-// Buffers of one lattice as byte offsets into the batch's single allocation,
-// whose base the kernels take as an argument: addresses formed from a kernel
-// argument are known to be global memory, so the loads and stores use a
-// scalar base (pointers read from device memory would be generic and turn
-// every access into a flat one with a 64-bit per-lane address).
-template <typename C>
-struct CavityDesc {
-  long long pop[2];  // population buffers (storage type), ping-pong
-  long long phi;     // per-node porosity, or -1
-  long long hv;      // per-node interphase coefficient, or -1
-  long long mac;     // macros of the last step (5 planes of nx*ny)
-  int tile_begin;    // first entry of this lattice in the combined tile list
-  int wave_begin;    // first entry of this lattice in the two-step wavefront list
-  int rows2;         // chunk height of its two-step wavefronts
-  int pad_;
-};
-
-template <typename T>
-__device__ __forceinline__ T* at_offset(char* base, long long off) {
-  return off < 0 ? nullptr : reinterpret_cast<T*>(base + off);
-}
 
 // Grid barrier state, zeroed by the host before each persistent launch.
 struct BatchCtl {
@@ -157,45 +138,6 @@ __global__ __launch_bounds__(kBlock) void batch_kernel(
   }
 }
 
-// Two steps of every lattice (FP32 form) in one launch: wavefront w runs
-// strip and chunk w - wave_begin of lattice wave_cav[w], as the
-// single-lattice two-step kernel does; with kMacros in F the second step
-// also writes each lattice's macros.
-template <int F>
-__global__ __launch_bounds__(kBatch2Block) void batch2_kernel(char* base, const CavityDesc<float>* __restrict__ cav,
-                                                        const StepConsts<float>* __restrict__ ks,
-                                                        const int* __restrict__ wave_cav, int nwaves, int per_xcd,
-                                                        int parity, uint32_t step) {
-  const int b = blockIdx.x;
-  const int blk = (b & (kXcds - 1)) * per_xcd + (b >> 3);
-  const int wl = static_cast<int>(threadIdx.x) >> 6;
-  const int wave = blk * (kBatch2Block / 64) + wl;
-  if (wave >= nwaves) return;  // whole wavefronts
-  const int c = __builtin_amdgcn_readfirstlane(wave_cav[wave]);
-  const StepConsts<float>& k = ks[c];
-  // this wavefront's lattice's binary64 temperature constants in LDS (see
-  // step2_kernel), copied by its own lanes into its own slot.  No workgroup
-  // barrier: a wavefront's LDS operations execute in order, so its reads see
-  // its own writes (and a barrier would make the compiler treat the
-  // parameter table as possibly written, loading it into vector registers).
-  __shared__ ThermalK<double> kts[kBatch2Block / 64];
-  {
-    constexpr int words = sizeof(ThermalK<double>) / 8;
-    static_assert(sizeof(ThermalK<double>) % 8 == 0 && words <= 64, "constant block too large");
-    const int lane = static_cast<int>(threadIdx.x) & 63;
-    if (lane < words)
-      reinterpret_cast<unsigned long long*>(&kts[wl])[lane] = reinterpret_cast<const unsigned long long*>(&k.td)[lane];
-    __builtin_amdgcn_wave_barrier();
-  }
-  const CavityDesc<float>& d = cav[c];
-  const int local = wave - d.wave_begin;
-  const int nstrips = (k.nx + step2_out(k.px) - 1) / step2_out(k.px);
-  float* mac = (F & kMacros) ? at_offset<float>(base, d.mac) : nullptr;
-  step2_wave<F, float>(at_offset<const float>(base, d.pop[parity]), at_offset<float>(base, d.pop[parity ^ 1]),
-                at_offset<const float>(base, d.phi), at_offset<const float>(base, d.hv), mac, k,
-                kts[wl], local % nstrips, local / nstrips, d.rows2, step);
-}
-
 // Threads per workgroup of the persistent two-step kernel: one workgroup of
 // eight wavefronts fills a CU at two wavefronts per SIMD, so the grid
 // barrier has one participant per CU.
@@ -244,8 +186,10 @@ __global__ __launch_bounds__(kPersistBlock) void batch2p_kernel(
       if (w >= w1) break;
       const int c = __builtin_amdgcn_readfirstlane(wave_cav[w]);
       const StepConsts<float>& k = *(const StepConsts<float>*)&ks[c];
-      // this item's lattice constants into the wavefront's own LDS slot (its
-      // LDS operations execute in order; see batch2_kernel)
+      // this item's lattice's binary64 temperature constants into the
+      // wavefront's own LDS slot (vector operands, which free the scalar
+      // registers; no workgroup barrier: a wavefront's LDS operations execute
+      // in order, so its reads see its own writes)
       if (lane < words)
         reinterpret_cast<unsigned long long*>(&kts[wl])[lane] =
             reinterpret_cast<const unsigned long long*>(&k.td)[lane];
@@ -274,14 +218,16 @@ struct lbm_ltne_batch {
   std::vector<lbm_ltne_params> p;
   std::vector<lbm_ltne_derived> d;
   std::vector<int> shift;  // tile width shift per lattice
-  std::vector<int> rows2;  // chunk height of the two-step launches per lattice
+  std::vector<int> rows2;  // chunk height of the persistent two-step launch per lattice
+  std::vector<TileGrid> tiles2;  // tiles of the two-step launches per lattice
   char* base = nullptr;    // all device memory of the batch
   size_t bytes = 0;
   std::vector<size_t> off_pop0, off_pop1, off_phi, off_hv, off_mac;
-  size_t off_cav = 0, off_consts = 0, off_tiles = 0, off_waves = 0, off_ctl = 0, off_result = 0;
+  size_t off_cav = 0, off_consts = 0, off_tiles = 0, off_waves = 0, off_tiles2 = 0, off_ctl = 0, off_result = 0;
   int nwaves2 = 0;    // wavefronts of a two-step launch over every lattice (current chunk heights)
   int nwaves2_min = 0;  // the same at the smallest chunk height (decides whether to use it; table size)
   bool step2_addr = true;  // every lattice's rows addressable by the two-step kernel
+  int ntiles2 = 0;    // tiles of a two-step launch over every lattice (0: single steps)
   int ntiles = 0;
   int max_tiles = 0;
   int fields = 0;     // kPhiField / kHvField if any lattice has that field
@@ -308,7 +254,8 @@ template <typename C>
 int upload_tables_t(lbm_ltne_batch* b) {
   std::vector<StepConsts<C>> ks(b->n);
   std::vector<CavityDesc<C>> cav(b->n);
-  std::vector<int> tile_cav, wave_cav;
+  std::vector<int> tile_cav, wave_cav, tile2_cav;
+  tile2_cav.reserve(b->ntiles2);
   tile_cav.reserve(b->max_tiles);
   wave_cav.reserve(b->nwaves2_min);
   for (int i = 0; i < b->n; ++i) {
@@ -323,7 +270,12 @@ int upload_tables_t(lbm_ltne_batch* b) {
     for (int t = 0; t < ks[i].tm.ntiles; ++t) tile_cav.push_back(i);
     cav[i].wave_begin = static_cast<int>(wave_cav.size());
     cav[i].rows2 = b->rows2[i];
+    cav[i].tile2_begin = static_cast<int>(tile2_cav.size());
+    cav[i].tile2_w = b->tiles2[i].w;
+    cav[i].tile2_h = b->tiles2[i].h;
+    cav[i].tile2_ntx = b->tiles2[i].ntx;
     cav[i].pad_ = 0;
+    for (int t = 0; t < b->tiles2[i].ntiles; ++t) tile2_cav.push_back(i);
     for (int w = 0; w < step2_waves(b->p[i].nx, b->p[i].ny, b->p[i].periodic_x, b->rows2[i]); ++w)
       wave_cav.push_back(i);
   }
@@ -334,6 +286,8 @@ int upload_tables_t(lbm_ltne_batch* b) {
   HIP_TRY(hipMemcpyAsync(b->base + b->off_cav, cav.data(), cav.size() * sizeof(cav[0]),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(b->base + b->off_tiles, tile_cav.data(), tile_cav.size() * sizeof(int),
+                         hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(hipMemcpyAsync(b->base + b->off_tiles2, tile2_cav.data(), tile2_cav.size() * sizeof(int),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(b->base + b->off_waves, wave_cav.data(), wave_cav.size() * sizeof(int),
                          hipMemcpyHostToDevice, b->stream));
@@ -391,43 +345,32 @@ int resident_grid(const lbm_ltne_batch* b, int* out, const void* fn = nullptr, i
 
 constexpr unsigned kSpinLimit = 1u << 24;
 
-template <int F>
-void launch_batch2_f(const lbm_ltne_batch* b, int parity, uint32_t step, bool macros) {
-  const CavityDesc<float>* cav = reinterpret_cast<const CavityDesc<float>*>(b->base + b->off_cav);
-  const StepConsts<float>* ks = reinterpret_cast<const StepConsts<float>*>(b->base + b->off_consts);
-  const int* waves = reinterpret_cast<const int*>(b->base + b->off_waves);
-  const int nblocks = (b->nwaves2 + kBatch2Block / 64 - 1) / (kBatch2Block / 64);
-  const int per_xcd = (nblocks + kXcds - 1) / kXcds;
-  const dim3 grid(kXcds * per_xcd), block(kBatch2Block);
-  if (macros)
-    hipLaunchKernelGGL(batch2_kernel<F | kMacros>, grid, block, 0, b->stream, b->base, cav, ks, waves, b->nwaves2,
-                       per_xcd, parity, step);
-  else
-    hipLaunchKernelGGL(batch2_kernel<F>, grid, block, 0, b->stream, b->base, cav, ks, waves, b->nwaves2, per_xcd,
-                       parity, step);
-}
-
 // A two-step launch over every lattice; macros: the second step also writes
 // the macros.
 hipError_t launch_batch2(const lbm_ltne_batch* b, int parity, uint32_t step, bool macros = false) {
-  switch (b->fields) {
-    case kPhiField: launch_batch2_f<kPhiField>(b, parity, step, macros); break;
-    case kHvField: launch_batch2_f<kHvField>(b, parity, step, macros); break;
-    case kPhiField | kHvField: launch_batch2_f<kPhiField | kHvField>(b, parity, step, macros); break;
-    default: launch_batch2_f<0>(b, parity, step, macros);
-  }
-  return hipGetLastError();
+  BatchTileLaunch a{};
+  a.base = b->base;
+  a.cav = b->base + b->off_cav;
+  a.consts = b->base + b->off_consts;
+  a.tile_cav = reinterpret_cast<const int*>(b->base + b->off_tiles2);
+  a.ntiles = b->ntiles2;
+  a.fields = b->fields;
+  a.parity = parity;
+  a.macros = macros;
+  a.step = step;
+  a.stream = b->stream;
+  return launch_batch_tile2(b->precision, a);
 }
 
 // FP32 batches with enough wavefronts at the smallest chunk height, whose
-// rows the two-step kernel can address, run pairs of steps per launch.
-bool two_step_ok(const lbm_ltne_batch* b) {
-  return b->precision == LBM_FP32 && b->step2_addr && b->nwaves2_min >= LTNE_STEP2_MIN_WAVES;
+// rows the kernel can address, run pairs of steps in the persistent launch.
+bool persist_pairs_ok(const lbm_ltne_batch* b) {
+  return b->precision == LBM_FP32 && b->step2_addr && b->nwaves2_min >= kPersistMinWaves;
 }
 
-// nsteps steps of every lattice.  Per-step mode: the FP32 form runs pairs
-// of steps in one two-step launch (two_step, and enough wavefronts), an odd
-// last step alone; the last launch writes the macros (macros_last).  The
+// nsteps steps of every lattice.  Per-step mode: pairs of steps in one
+// two-step launch (two_step), an odd last step alone; the last launch writes
+// the macros (macros_last).  The
 // autotuner's tile trials run single steps only (the tile widths it chooses
 // apply to them).
 int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step = true) {
@@ -439,8 +382,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
   BatchCtl* ctl = reinterpret_cast<BatchCtl*>(b->base + b->off_ctl);
   int ntiles = b->ntiles;
   unsigned spin = kSpinLimit;
-  const bool two_ok = two_step && two_step_ok(b);
-  if (b->persistent && two_ok) {
+  if (b->persistent && two_step && persist_pairs_ok(b)) {
     // the pairs of steps in one persistent launch, then the remaining single
     // step (the one that writes the macros) as an ordinary launch
     int npairs = (nsteps - (macros_last ? 1 : 0)) / 2;
@@ -475,7 +417,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
   } else {
     const int per = (ntiles + kXcds - 1) / kXcds;
     const int grid = kXcds * per;  // one tile per workgroup per step
-    const bool two = two_ok;
+    const bool two = two_step && b->ntiles2 > 0;
     int parity = b->parity;
     for (int s = 0; s < nsteps;) {
       const uint32_t step0 = static_cast<uint32_t>(b->steps + 1 + s);
@@ -605,6 +547,9 @@ int lbm_ltne_batch_create(int32_t n, const lbm_ltne_params* ps, const double* co
   b->d = ds;
   b->shift.assign(n, 0);
   b->rows2.assign(n, kBatch2Rows);
+  b->tiles2.resize(n);
+  tile2_batch_grids(n, ps, b->tiles2.data());
+  for (const TileGrid& g : b->tiles2) b->ntiles2 += g.ntiles;
   for (int i = 0; i < n; ++i) {
     if (phi_fields && phi_fields[i]) b->fields |= kPhiField;
     if (Hv_fields && Hv_fields[i]) b->fields |= kHvField;
@@ -641,6 +586,7 @@ int lbm_ltne_batch_create(int32_t n, const lbm_ltne_params* ps, const double* co
   b->off_cav = o; o += align_up(n * b->desc_bytes, kAlign);
   b->off_tiles = o; o += align_up(static_cast<size_t>(b->max_tiles) * sizeof(int), kAlign);
   b->off_waves = o; o += align_up(static_cast<size_t>(b->nwaves2_min) * sizeof(int), kAlign);
+  b->off_tiles2 = o; o += align_up(static_cast<size_t>(b->ntiles2) * sizeof(int), kAlign);
   b->off_ctl = o; o += kAlign;
   b->off_result = o; o += kAlign;
   b->bytes = o;
@@ -716,7 +662,7 @@ int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t* nodes, int32_t* tiles, int3
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
   if (nodes) *nodes = b->nodes;
   if (tiles) *tiles = b->ntiles;
-  if (grid) *grid = two_step_ok(b) ? b->grid2 : b->grid;
+  if (grid) *grid = persist_pairs_ok(b) ? b->grid2 : b->grid;
   if (persistent) *persistent = b->persistent;
   return LBM_OK;
 }
@@ -827,28 +773,31 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     }
     for (int i : kv.second) b->shift[i] = best_shift;
   }
-  // The chunk heights of the two-step launches (FP32 form), timed on the
-  // path that runs: pairs of steps per launch over every lattice.
-  const bool two = two_step_ok(b);
-  if (two && rc == LBM_OK) {
-    auto trial2 = [&](float* ms) -> int {
-      int r = copy_state(false);
-      if (r != LBM_OK) return r;
-      b->parity = parity0;
-      r = launch_batch(b, 2, 0, true);  // warm-up
-      if (r != LBM_OK) return r;
-      HIP_TRY(hipEventRecord(e0, b->stream));
-      r = launch_batch(b, 2 * reps, 0, true);
-      if (r != LBM_OK) return r;
-      HIP_TRY(hipEventRecord(e1, b->stream));
-      HIP_TRY(hipEventSynchronize(e1));
-      HIP_TRY(hipEventElapsedTime(ms, e0, e1));
-      *ms /= static_cast<float>(2 * reps);
-      b->parity = parity0;
-      return LBM_OK;
-    };
-    rc = upload_tables(b);
-    if (rc == LBM_OK) rc = trial2(&best);
+  // Time per step over 2 reps steps of launch mode m, from the snapshot.
+  const int mode0 = b->persistent;
+  auto trial2 = [&](int m, float* ms) -> int {
+    b->persistent = m;
+    int r = copy_state(false);
+    if (r != LBM_OK) return r;
+    b->parity = parity0;
+    r = launch_batch(b, 2, 0, true);  // warm-up
+    if (r != LBM_OK) return r;
+    HIP_TRY(hipEventRecord(e0, b->stream));
+    r = launch_batch(b, 2 * reps, 0, true);
+    if (r != LBM_OK) return r;
+    HIP_TRY(hipEventRecord(e1, b->stream));
+    HIP_TRY(hipEventSynchronize(e1));
+    HIP_TRY(hipEventElapsedTime(ms, e0, e1));
+    r = check_ctl(b);
+    *ms /= static_cast<float>(2 * reps);
+    b->parity = parity0;
+    return r;
+  };
+  if (rc == LBM_OK) rc = upload_tables(b);
+  // The chunk heights of the persistent two-step launch (FP32 form).
+  const bool can_persist = b->grid >= kXcds && !(b->precision == LBM_FP32 && b->grid2 < kXcds);
+  if (rc == LBM_OK && can_persist && persist_pairs_ok(b)) {
+    rc = trial2(1, &best);
     for (auto& kv : classes) {
       if (rc != LBM_OK) break;
       int best_rows = b->rows2[kv.second[0]];
@@ -857,7 +806,7 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
         for (int i : kv.second) b->rows2[i] = r;
         rc = upload_tables(b);
         float ms = 0.0f;
-        if (rc == LBM_OK) rc = trial2(&ms);
+        if (rc == LBM_OK) rc = trial2(1, &ms);
         if (rc != LBM_OK) break;
         if (ms < best) {
           best = ms;
@@ -866,38 +815,18 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
       }
       for (int i : kv.second) b->rows2[i] = best_rows;
     }
+    if (rc == LBM_OK) rc = upload_tables(b);
   }
-  if (rc == LBM_OK) rc = upload_tables(b);
-  // The launch mode, with the shapes chosen: both modes timed over 2 reps
-  // steps of the path each runs (pairs of steps where they apply), from the
-  // snapshot; the faster is kept.  Persistent launches pay off where
-  // launches are a large part of a step (small batches).
-  const bool can_persist = b->grid >= kXcds && !(b->precision == LBM_FP32 && b->grid2 < kXcds);
-  if (rc == LBM_OK && can_persist) {
-    const int mode0 = b->persistent;
+  // The launch mode, with the shapes chosen: each mode timed on the path it
+  // runs; the faster is kept.  Persistent launches pay off where launches are
+  // a large part of a step (small batches).
+  if (rc == LBM_OK) {
     float ms_mode[2] = {0.0f, 0.0f};
-    for (int m = 0; m < 2 && rc == LBM_OK; ++m) {
-      b->persistent = m;
-      rc = copy_state(false);
-      b->parity = parity0;
-      if (rc == LBM_OK) rc = launch_batch(b, 2, 0, true);  // warm-up
-      if (rc == LBM_OK && hipEventRecord(e0, b->stream) != hipSuccess) rc = set_error(LBM_EHIP, "event record");
-      if (rc == LBM_OK) rc = launch_batch(b, 2 * reps, 0, true);
-      if (rc == LBM_OK && hipEventRecord(e1, b->stream) != hipSuccess) rc = set_error(LBM_EHIP, "event record");
-      if (rc == LBM_OK && hipEventSynchronize(e1) != hipSuccess) rc = set_error(LBM_EHIP, "event sync");
-      if (rc == LBM_OK && hipEventElapsedTime(&ms_mode[m], e0, e1) != hipSuccess)
-        rc = set_error(LBM_EHIP, "event time");
-      if (rc == LBM_OK) rc = check_ctl(b);
-      ms_mode[m] /= static_cast<float>(2 * reps);
-    }
-    b->parity = parity0;
-    if (rc == LBM_OK) {
-      b->persistent = ms_mode[1] < ms_mode[0] ? 1 : 0;
-      best = ms_mode[b->persistent];
-    } else {
-      b->persistent = mode0;
-    }
+    for (int m = 0; m < (can_persist ? 2 : 1) && rc == LBM_OK; ++m) rc = trial2(m, &ms_mode[m]);
+    b->persistent = can_persist && ms_mode[1] < ms_mode[0] ? 1 : 0;
+    best = ms_mode[b->persistent];
   }
+  if (rc != LBM_OK) b->persistent = mode0;
   const int rc2 = copy_state(false);
   if (rc == LBM_OK) rc = rc2;
   if (hipStreamSynchronize(b->stream) != hipSuccess && rc == LBM_OK) rc = set_error(LBM_EHIP, "autotune sync");

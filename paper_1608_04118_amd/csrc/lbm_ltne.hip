@@ -15,7 +15,7 @@
 #include "reduce_kernels.hpp"
 #include "adjoint_kernel.hpp"
 #include "step_kernel.hpp"
-#include "step2_kernel.hpp"
+#include "tile_launch.hpp"
 
 using namespace ltne;
 
@@ -34,6 +34,7 @@ struct lbm_ltne {
   StepConsts<double> kd{};
   StepConsts<float> kf{};
   std::vector<double> tf0, ts0;  // initial temperature fields (if given), for the adjoint
+  TileGrid tiles{};  // tiles of the two-step launches
   hipGraphExec_t seq[2] = {nullptr, nullptr};  // recorded runs of kSeqSteps steps from buffer 0 / 1
 
   void* pop(int i) const { return base + lay.off_pop[i]; }
@@ -140,57 +141,20 @@ hipError_t launch_step(const lbm_ltne* h, int mode, int64_t step, const void* sr
 }
 
 
-// Geometry of the two-step kernel: strips of 64 lanes (63 - halo output
-// columns), chunks of step2_rows() rows, kStep2Block / 64 wavefronts per workgroup,
-// workgroups dealt to the XCDs in contiguous ranges.
-Step2Map step2_map(const lbm_ltne_params& p) {
-  Step2Map m{};
-  m.halo = step2_halo(p.periodic_x);
-  m.out = step2_out(p.periodic_x);
-  m.nstrips = (p.nx + m.out - 1) / m.out;
-  m.rows = step2_rows(p.nx, p.ny, p.periodic_x, storage_bytes(p.precision));
-  m.nchunks = (p.ny + m.rows - 1) / m.rows;
-  m.nwaves = m.nstrips * m.nchunks;
-  const int nblocks = (m.nwaves + kStep2Block / 64 - 1) / (kStep2Block / 64);
-  m.per_xcd = (nblocks + kXcds - 1) / kXcds;
-  return m;
-}
-
-// Two steps in one launch (FP32 and FP64 forms); with mac, the second step
-// also writes the macros (the last two steps of a call).
-template <typename S, int F>
-void launch_step2_t(const lbm_ltne* h, const StepConsts<S>& k, const Step2Map& m, const S* s, S* d, S* mac,
-                    uint32_t st) {
-  const dim3 grid(kXcds * m.per_xcd), block(kStep2Block);
-  const S* phi = static_cast<const S*>(h->phi());
-  const S* hv = static_cast<const S*>(h->hv());
-  if (mac)
-    hipLaunchKernelGGL((step2_kernel<S, F | kMacros>), grid, block, 0, h->stream, s, d, phi, hv, mac, k, m, st);
-  else
-    hipLaunchKernelGGL((step2_kernel<S, F>), grid, block, 0, h->stream, s, d, phi, hv, mac, k, m, st);
-}
-
-template <typename S>
-void launch_step2_s(const lbm_ltne* h, const StepConsts<S>& k, uint32_t st, const void* src, void* dst, void* mac) {
-  const Step2Map m = step2_map(h->p);
-  const S* s = static_cast<const S*>(src);
-  S* d = static_cast<S*>(dst);
-  S* mc = static_cast<S*>(mac);
-  switch ((h->has_phi ? kPhiField : 0) | (h->has_hv ? kHvField : 0)) {
-    case 0: launch_step2_t<S, 0>(h, k, m, s, d, mc, st); break;
-    case kPhiField: launch_step2_t<S, kPhiField>(h, k, m, s, d, mc, st); break;
-    case kHvField: launch_step2_t<S, kHvField>(h, k, m, s, d, mc, st); break;
-    default: launch_step2_t<S, kPhiField | kHvField>(h, k, m, s, d, mc, st);
-  }
-}
-
+// Two steps in one launch; with mac, the second step also writes the macros
+// (the last two steps of a call).
 hipError_t launch_step2(const lbm_ltne* h, int64_t step, const void* src, void* dst, void* mac = nullptr) {
-  const uint32_t st = static_cast<uint32_t>(step);
-  if (h->p.precision == LBM_FP64)
-    launch_step2_s<double>(h, h->kd, st, src, dst, mac);
-  else
-    launch_step2_s<float>(h, h->kf, st, src, dst, mac);
-  return hipGetLastError();
+  TileLaunch a{};
+  a.consts = compute_bytes(h->p.precision) == 8 ? static_cast<const void*>(&h->kd) : static_cast<const void*>(&h->kf);
+  a.src = src;
+  a.dst = dst;
+  a.phi = h->phi();
+  a.hv = h->hv();
+  a.mac = mac;
+  a.grid = h->tiles;
+  a.step = static_cast<uint32_t>(step);
+  a.stream = h->stream;
+  return launch_tile2(h->p.precision, a);
 }
 
 // Copies a host double field to device memory in the compute type.
@@ -421,6 +385,7 @@ int lbm_ltne_create(const lbm_ltne_params* p, const double* phi_field, const dou
   }
   fill_consts(h, &h->kd);
   fill_consts(h, &h->kf);
+  h->tiles = tile2_grid(h->p);
 
   rc = LBM_OK;
   if (phi_field) rc = upload_field(h, phi_field, h->phi());
@@ -474,14 +439,7 @@ int lbm_ltne_step(lbm_ltne_t h, int64_t nsteps) {
   if (!h) return set_error(LBM_EINVAL, "handle is NULL");
   if (nsteps < 0) return set_error(LBM_EINVAL, "nsteps = %lld < 0", static_cast<long long>(nsteps));
   if (nsteps == 0) return LBM_OK;
-  // two steps per launch where the lattice gives the two-step kernel enough
-  // wavefronts to hide its latency (each wavefront runs a serial chain of
-  // rows); small lattices run faster one step at a time
-  const bool fp64 = h->p.precision == LBM_FP64;
-  const bool pairs = (h->p.precision == LBM_FP32 || fp64) &&
-                     step2_addressable(h->p.nx, storage_bytes(h->p.precision)) &&
-                     step2_waves(h->p.nx, h->p.ny, h->p.periodic_x, kStep2MinRows) >=
-                         (fp64 ? LTNE_STEP2_MIN_WAVES_64 : LTNE_STEP2_MIN_WAVES);
+  const bool pairs = h->tiles.ntiles > 0;
   const int64_t de = h->p.diag_every;
   auto checked = [de](int64_t t) { return de > 0 && t % de == 0; };
   void* scratch_mac = h->mac(1 - h->mcur);  // overwritten by the call's last step

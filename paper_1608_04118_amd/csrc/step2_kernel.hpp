@@ -1,8 +1,7 @@
-// Two fused time steps per launch for the FP32 form (binary32 storage,
-// binary32 flow and binary64 temperature arithmetic) and the FP64 form (the
-// same code over binary64 populations).  The single-step kernel is bound by
-// memory traffic; computing two steps per pass over the populations halves
-// the traffic per lattice-node update.
+// Two fused time steps per pass over the populations for the persistent
+// batch launch of the FP32 form (binary32 storage, binary32 flow and binary64
+// temperature arithmetic), whose wavefronts take strips of uneven lattices
+// from a counter.  (The ordinary launches hold tiles in LDS, tile_kernel.hpp.)
 //
 // Each wavefront owns a strip of columns and a chunk of rows and marches
 // down the rows.  Lane l holds column x0 - H + l (H = 1 on a periodic x axis,
@@ -24,63 +23,16 @@
 
 namespace ltne {
 
-// Rows per chunk.  A chunk recomputes two halo rows at the intermediate time
-// level, so taller chunks do less redundant work but leave fewer wavefronts
-// in flight.  A single lattice takes the tallest of kStep2RowChoices that
-// still yields kStep2TargetWaves wavefronts; a batch of lattices (many small
-// ones) uses kBatch2Rows.  The binary64 kernel holds one wavefront per SIMD
-// (it needs more than half the register file), so it fills the chip with
-// half the wavefronts and may take chunks of 64 rows.  LTNE_STEP2_ROWS
-// forces one height (experiments).
-constexpr int kStep2RowChoices[] = {64, 32, 24, 16, 12, 8};
-constexpr int kStep2MaxRows32 = 32;  // tallest chunk of the binary32 kernel
-constexpr int kStep2MinRows = 8;
-// chunk heights a batch may take (chosen per size class by the autotuner)
+// Rows per chunk, per size class of the batch (chosen by the autotuner).  A
+// chunk recomputes two halo rows at the intermediate time level, so taller
+// chunks do less redundant work but leave fewer wavefronts in flight.
 constexpr int kBatch2RowChoices[] = {32, 24, 16, 12, 8};
-#ifndef LTNE_STEP2_TARGET_WAVES
-#define LTNE_STEP2_TARGET_WAVES 16384
-#endif
-constexpr int kStep2TargetWaves = LTNE_STEP2_TARGET_WAVES;
-#ifndef LTNE_BATCH2_ROWS
-#define LTNE_BATCH2_ROWS 16
-#endif
-constexpr int kBatch2Rows = LTNE_BATCH2_ROWS;
-// Threads per workgroup of the two-step kernels (whole wavefronts; each
-// wavefront works on its own strip and chunk).
-#ifndef LTNE_STEP2_BLOCK
-#define LTNE_STEP2_BLOCK 256
-#endif
-constexpr int kStep2Block = LTNE_STEP2_BLOCK;
-static_assert(kStep2Block % 64 == 0 && kStep2Block <= 1024, "whole wavefronts per workgroup");
-// Threads per workgroup of the batched two-step kernel: one wavefront, so a
-// compute unit starts a new strip as soon as any of its wavefronts ends (the
-// strips of small lattices differ in length; on the 256-cavity batch one
-// wavefront per workgroup was 5% faster than four, while a single large
-// lattice runs faster with four neighbouring strips per workgroup).
-#ifndef LTNE_BATCH2_BLOCK
-#define LTNE_BATCH2_BLOCK 64
-#endif
-constexpr int kBatch2Block = LTNE_BATCH2_BLOCK;
-static_assert(kBatch2Block % 64 == 0 && kBatch2Block <= 1024, "whole wavefronts per workgroup");
-// Stores of the two-step kernels: plain, so the L2 merges the partial cache
-// lines written by neighbouring strips (62 or 61 columns wide) before they go
-// to HBM; non-temporal stores were 5% slower on the 8192^2 layer.
-#ifndef LTNE_STEP2_NT_STORE
-#define LTNE_STEP2_NT_STORE 0
-#endif
-constexpr bool kStep2NtStore = LTNE_STEP2_NT_STORE != 0;
-// Two-step launches need this many wavefronts at the smallest chunk height
-// to hide the serial chain of rows each one runs; with fewer, single steps
-// are faster (the FP32 layer: 640^2 with 880 wavefronts 2% slower in pairs,
-// 768^2 with 1248 2% faster).  The binary64 kernel runs one wavefront per
-// SIMD and needs more (the FP64 layer: 1024^2 with 2176 wavefronts 2% slower
-// in pairs, 1152^2 with 2736 13% faster).
-#ifndef LTNE_STEP2_MIN_WAVES
-#define LTNE_STEP2_MIN_WAVES 1024
-#endif
-#ifndef LTNE_STEP2_MIN_WAVES_64
-#define LTNE_STEP2_MIN_WAVES_64 2560
-#endif
+constexpr int kStep2MinRows = 8;
+constexpr int kBatch2Rows = 16;  // default
+// The persistent launch runs pairs of steps from this many wavefronts at the
+// smallest chunk height on, enough to hide the serial chain of rows that each
+// one runs.
+constexpr int kPersistMinWaves = 1024;
 
 // Lanes left of a strip's first output column: one on a periodic x axis,
 // two with x walls (a wall node pulls from two columns inward).
@@ -89,32 +41,6 @@ __host__ __device__ constexpr int step2_out(int periodic_x) { return 63 - step2_
 __host__ __device__ constexpr int step2_waves(int nx, int ny, int periodic_x, int rows) {
   return ((nx + step2_out(periodic_x) - 1) / step2_out(periodic_x)) * ((ny + rows - 1) / rows);
 }
-// Chunk height of a single lattice's two-step launches (elem_bytes: 4 or 8,
-// the storage type).
-inline int step2_rows(int nx, int ny, int periodic_x, size_t elem_bytes) {
-#ifdef LTNE_STEP2_ROWS
-  (void)nx, (void)ny, (void)periodic_x, (void)elem_bytes;
-  return LTNE_STEP2_ROWS;
-#else
-  const bool wide = elem_bytes == 8;
-  const int target = wide ? kStep2TargetWaves / 2 : kStep2TargetWaves;
-  for (int r : kStep2RowChoices)
-    if ((wide || r <= kStep2MaxRows32) && step2_waves(nx, ny, periodic_x, r) >= target) return r;
-  return kStep2MinRows;
-#endif
-}
-
-// Launch geometry of the two-step kernel.
-struct Step2Map {
-  int halo;     // lanes left of the first output column (1 or 2)
-  int out;      // output columns per strip (63 - halo)
-  int nstrips;  // strips across the lattice
-  int rows;     // rows per chunk
-  int nchunks;  // chunks down the lattice
-  int nwaves;   // nstrips * nchunks
-  int per_xcd;  // workgroups per XCD
-};
-
 // Loads and stores of the two-step kernel through buffer resources: one
 // resource per lattice row (its 19 population rows), the population's offset
 // in the scalar offset operand and the lane's column in the vector offset,
@@ -125,22 +51,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const S* row, long lo
                                            static_cast<int>(rs * static_cast<long long>(sizeof(S))), 0x00020000);
 }
 
-// One element (binary32 or binary64) through a buffer resource.
+// One element through a buffer resource.
 template <typename S>
 __device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, int vo, int so) {
-  if constexpr (sizeof(S) == 8)
-    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
-  else
-    return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+  static_assert(sizeof(S) == 4, "binary32 storage");
+  return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
 }
-template <int Aux, typename S>
+template <typename S>
 __device__ __forceinline__ void buf_store(S v, __amdgpu_buffer_rsrc_t r, int vo, int so) {
-  if constexpr (sizeof(S) == 8) {
-    using W = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(W, v), r, vo, so, Aux);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, vo, so, Aux);
-  }
+  static_assert(sizeof(S) == 4, "binary32 storage");
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, vo, so, 0);
 }
 
 template <typename S>
@@ -206,8 +126,6 @@ __device__ __forceinline__ CenterFields<S> buf_center(const S* __restrict__ phi_
 
 template <typename S>
 struct BufPut {
-  // cache policy of the stores: the non-temporal bit when kStep2NtStore
-  static constexpr int kNtAux = kStep2NtStore ? 2 : 0;
   S* __restrict__ dst;
   __amdgpu_buffer_rsrc_t r;
   int vo = 0, Q = 0;
@@ -216,7 +134,7 @@ struct BufPut {
     vo = x * static_cast<int>(sizeof(S));
     Q = static_cast<int>(k.qs) * static_cast<int>(sizeof(S));
   }
-  __device__ __forceinline__ void st(int i, S v) { buf_store<kNtAux>(v, r, vo, i * Q); }
+  __device__ __forceinline__ void st(int i, S v) { buf_store(v, r, vo, i * Q); }
   template <typename VA, typename VB>
   __device__ __forceinline__ void pair(int i, VA va, VA, int j, VB vb, VB, uint32_t w, half2_t&) {
     st(i, to_storage<S>(va, w << 16));
@@ -225,15 +143,6 @@ struct BufPut {
   template <typename V>
   __device__ __forceinline__ void single(int i, V v, V, uint32_t w) { st(i, to_storage<S>(v, w)); }
 };
-
-// Copies a constant block into LDS, one 8-byte word per thread.
-template <typename K>
-__device__ __forceinline__ void copy_to_lds(const K& src, K& dst) {
-  static_assert(sizeof(K) % 8 == 0 && sizeof(K) / 8 <= 64, "constant block too large");
-  const int t = static_cast<int>(threadIdx.x);
-  if (t < static_cast<int>(sizeof(K) / 8))
-    reinterpret_cast<unsigned long long*>(&dst)[t] = reinterpret_cast<const unsigned long long*>(&src)[t];
-}
 
 // Put into registers: the 19 post-collision populations of one node, rounded
 // to the storage type exactly as a store to memory would round them (the
@@ -434,24 +343,6 @@ __device__ __forceinline__ void step2_wave(const S* __restrict__ src, S* __restr
     }
     fy = fn;
   }
-}
-
-template <typename S, int F>
-__global__ __launch_bounds__(kStep2Block) void step2_kernel(const S* __restrict__ src, S* __restrict__ dst,
-                                                       const S* __restrict__ phi_field,
-                                                       const S* __restrict__ hv_field,
-                                                       S* __restrict__ mac, const StepConsts<S> k,
-                                                       const Step2Map m, const uint32_t step) {
-  const int b = blockIdx.x;
-  const int blk = (b & (kXcds - 1)) * m.per_xcd + (b >> 3);
-  const int wave = blk * (kStep2Block / 64) + (static_cast<int>(threadIdx.x) >> 6);
-  // the binary64 temperature constants as vector operands from LDS rather
-  // than scalar registers (which the kernel runs short of)
-  __shared__ ThermalK<double> kt;
-  copy_to_lds(k.td, kt);
-  __syncthreads();
-  if (wave >= m.nwaves) return;  // whole wavefronts
-  step2_wave<F>(src, dst, phi_field, hv_field, mac, k, kt, wave % m.nstrips, wave / m.nstrips, m.rows, step);
 }
 
 }  // namespace ltne

@@ -544,13 +544,15 @@ __device__ __forceinline__ void node_update_with(
     nh0 = D + T(0.5) * dsr;
   }
 
-  if constexpr ((F & kMacros) != 0) {
-    const int ib = y * nx + x;
-    mac[0 * k.mplane + ib] = rho;
-    mac[1 * k.mplane + ib] = ux;
-    mac[2 * k.mplane + ib] = uy;
-    mac[3 * k.mplane + ib] = C(thf + kt.T_ref);
-    mac[4 * k.mplane + ib] = C(ths + kt.T_ref);
+  if constexpr ((F & (kMacros | kMacrosIf)) != 0) {
+    if ((F & kMacros) != 0 || mac != nullptr) {
+      const int ib = y * nx + x;
+      mac[0 * k.mplane + ib] = rho;
+      mac[1 * k.mplane + ib] = ux;
+      mac[2 * k.mplane + ib] = uy;
+      mac[3 * k.mplane + ib] = C(thf + kt.T_ref);
+      mac[4 * k.mplane + ib] = C(ths + kt.T_ref);
+    }
   }
 
   const int io = y * nx + x;  // node index (hash input)

@@ -1,0 +1,90 @@
+// Host interface of the tiled two-step kernels (tile_kernel.hpp), which are
+// compiled apart from the rest of the library (tile.hip, one object per
+// precision form).
+#pragma once
+
+#include "common.hpp"
+#include "lbm_ltne.h"
+
+namespace ltne {
+
+// Buffers of one lattice as byte offsets into the batch's single allocation,
+// whose base the kernels take as an argument: addresses formed from a kernel
+// argument are known to be global memory, so the loads and stores use a
+// scalar base (pointers read from device memory would be generic and turn
+// every access into a flat one with a 64-bit per-lane address).
+template <typename C>
+struct CavityDesc {
+  long long pop[2];  // population buffers (storage type), ping-pong
+  long long phi;     // per-node porosity, or -1
+  long long hv;      // per-node interphase coefficient, or -1
+  long long mac;     // macros of the last step (5 planes of nx*ny)
+  int tile_begin;    // first entry of this lattice in the combined tile list
+  int wave_begin;    // first entry of this lattice in the two-step wavefront list
+  int rows2;         // chunk height of its two-step wavefronts
+  int tile2_begin;   // first entry of this lattice in the two-step tile list
+  int tile2_w, tile2_h, tile2_ntx;  // its two-step tiles
+  int pad_;
+};
+
+template <typename T>
+__device__ __forceinline__ T* at_offset(char* base, long long off) {
+  return off < 0 ? nullptr : reinterpret_cast<T*>(base + off);
+}
+
+// Tiles of a two-step launch over one lattice.
+struct TileGrid {
+  int w, h;     // output nodes of a tile, (w + 2) (h + 2) at most the kernel's slots
+  int ntx;      // tiles along x
+  int ntiles;   // tiles of the lattice (0: the lattice does not take two-step tiles)
+  int per_xcd;  // tiles per XCD; the grid has 8 per_xcd workgroups
+};
+
+// LDS slots (nodes) and threads of a workgroup per precision form: two
+// workgroups share a CU's 160 KB (19 populations a slot, 81472 bytes a
+// workgroup) and its wavefront slots -- 4 wavefronts per SIMD in the forms
+// whose node update needs 80 to 128 registers, 8 with binary16 storage (64).
+inline int tile2_slots(int precision) { return precision == LBM_FP64 ? 536 : (precision == LBM_FP16S ? 2144 : 1072); }
+inline int tile2_block(int precision) { return precision == LBM_FP16S ? 1024 : 512; }
+
+// The tile shape of one lattice's two-step launches.
+TileGrid tile2_grid(const lbm_ltne_params& p);
+// Tile shapes of a batch's lattices (all of them, or none: ntiles = 0).
+void tile2_batch_grids(int n, const lbm_ltne_params* ps, TileGrid* out);
+
+struct TileLaunch {
+  const void* consts;  // StepConsts of the lattice (host)
+  const void* src;
+  void* dst;
+  const void* phi;
+  const void* hv;
+  void* mac;  // macros of the second step, or nullptr
+  TileGrid grid;
+  uint32_t step;  // number of the first of the two steps
+  hipStream_t stream;
+};
+hipError_t launch_tile2(int precision, const TileLaunch& a);
+
+struct BatchTileLaunch {
+  char* base;
+  const void* cav;      // CavityDesc of every lattice (device)
+  const void* consts;   // StepConsts of every lattice (device)
+  const int* tile_cav;  // lattice of every tile (device)
+  int ntiles, fields, parity;
+  bool macros;
+  uint32_t step;
+  hipStream_t stream;
+};
+hipError_t launch_batch_tile2(int precision, const BatchTileLaunch& a);
+
+// One object of tile.hip per form.
+hipError_t launch_tile2_f64(const TileLaunch& a);
+hipError_t launch_tile2_f32(const TileLaunch& a);
+hipError_t launch_tile2_f16s(const TileLaunch& a);
+hipError_t launch_tile2_f32sr(const TileLaunch& a);
+hipError_t launch_batch_tile2_f64(const BatchTileLaunch& a);
+hipError_t launch_batch_tile2_f32(const BatchTileLaunch& a);
+hipError_t launch_batch_tile2_f16s(const BatchTileLaunch& a);
+hipError_t launch_batch_tile2_f32sr(const BatchTileLaunch& a);
+
+}  // namespace ltne
