@@ -11,8 +11,9 @@ Eq. 52 correlation and the Sec. 3.2 correction term, are timed on the same
 lattice and reported under "variants".
 
 A step is one time step of all three lattices over the whole lattice.  Every
-form advances two steps per launch (an odd last step of a call alone; the
-call's last launch also writes the macroscopic fields).  Inputs are
+form advances three steps per launch (two, or one, where a call's number of
+steps leaves them over; the call's last launch also writes the macroscopic
+fields).  Inputs are
 resident in device memory before timing starts.  The time of K steps (one
 call) is taken with HIP events on the stream the library queues on, between
 two device synchronisations.
@@ -116,9 +117,8 @@ CUS, CLOCK_HZ = 256, 2.4e9
 VALU_ISSUE_PER_S = CUS * CLOCK_HZ
 
 
-# Forms whose steps run two to a launch on the 8192^2 layer (an odd last step
-# of a call alone)
-TWO_STEP = ("f32", "f32ext", "f64", "f16s", "f32sr")
+# Steps of a launch on the 8192^2 layer (every form)
+STEPS_PER_LAUNCH = 3
 
 
 def _events_ms(stream, fn):
@@ -135,9 +135,9 @@ def _events_ms(stream, fn):
 
 def time_form(tag: str, steps: int, warmup: int, inputs):
     """Whole-job rate over `steps` steps of one call (every launch the call
-    makes).  For the two-step forms, also the average duration of one
-    two-step launch: a call of 2m + 1 steps (m two-step launches and the
-    final single step that writes the macros) minus a call of one step."""
+    makes), and the average duration of one launch of STEPS_PER_LAUNCH steps:
+    a call of m + 1 launches (the last one writes the macros) minus a call of
+    one."""
     import torch
     from paper_1608_04118_amd import binding as B
     p, phi, Tf0, Ts0 = inputs
@@ -147,12 +147,11 @@ def time_form(tag: str, steps: int, warmup: int, inputs):
     if warmup:
         lat.step(warmup)
     ms = _events_ms(stream, lambda: lat.step(steps))
-    launch_ms, steps_per_launch = ms / steps, 1
-    if tag in TWO_STEP:
-        m = max(1, steps // 2)
-        t_call = _events_ms(stream, lambda: lat.step(2 * m + 1))
-        t_one = _events_ms(stream, lambda: lat.step(1))
-        launch_ms, steps_per_launch = (t_call - t_one) / m, 2
+    spl = STEPS_PER_LAUNCH
+    m = max(1, steps // spl)
+    t_call = _events_ms(stream, lambda: lat.step(spl * (m + 1)))
+    t_one = _events_ms(stream, lambda: lat.step(spl))
+    launch_ms, steps_per_launch = (t_call - t_one) / m, spl
     mass, energy, _ = lat.diagnostics()
     if not (np.isfinite(mass) and np.isfinite(energy)):
         raise RuntimeError("%s run diverged" % tag)
@@ -163,8 +162,8 @@ def time_form(tag: str, steps: int, warmup: int, inputs):
     ms_step = ms / steps
     mlups = cells * steps / (ms * 1e-3) / 1e6
     # HBM bytes one launch must move: every population read and written once
-    # and the porosity read once per node, whether the launch advances one
-    # step or two (the intermediate level of a two-step launch stays on chip)
+    # and the porosity read once per node, however many steps the launch
+    # advances (the levels between stay on chip)
     bytes_launch = BYTES_PER_LUP[tag] * cells
     achieved = bytes_launch / (launch_ms * 1e-3) / 1e9
     return dict(ms_per_step=ms_step, mlups=mlups, achieved_gbs=achieved,
@@ -175,8 +174,8 @@ def time_form(tag: str, steps: int, warmup: int, inputs):
 def time_batch(steps: int, warmup: int, autotune: bool = True):
     """The 256-cavity batch (sides 64..512, seeded parameters), FP32: tile
     widths, chunk heights and launch mode chosen by the autotuner, then both
-    launch modes timed (launches over all lattices, two steps per launch but
-    the last of a call; or one persistent launch); ms_per_step is the mode
+    launch modes timed (launches of three steps over all lattices; or one
+    persistent launch of pairs of steps); ms_per_step is the mode
     the autotuner chose.  Aggregate node updates per second."""
     import torch
     from paper_1608_04118_amd import binding as B
@@ -207,14 +206,15 @@ def time_batch(steps: int, warmup: int, autotune: bool = True):
     nodes = info["nodes"]
     ms_step = ms_persistent if chosen else ms_launches
     # one read and one write of the state (19 binary32 populations, uniform
-    # porosity) per two-step launch: 152 B per node per two steps
-    achieved = 152 * nodes / (2 * ms_step * 1e-3) / 1e9
+    # porosity) per launch of three steps (pairs in the persistent mode)
+    spl = 2 if chosen else STEPS_PER_LAUNCH
+    achieved = 152 * nodes / (spl * ms_step * 1e-3) / 1e9
     return dict(ms_per_step=ms_step, mlups=nodes / (ms_step * 1e-3) / 1e6, achieved_gbs=achieved,
                 frac=achieved / HBM_PEAK_GBS, nodes=nodes, lattices=len(ps), grid=info["grid"],
                 mode=("one persistent launch per call" if chosen else
-                      "launches over all lattices, two steps per launch (an odd last step alone)"),
+                      "launches over all lattices, three steps per launch"),
                 mode_chosen_by="autotuner" if autotune else "default",
-                bytes_note="152 B per node per pair of steps (state read and written once)",
+                bytes_note="152 B per node per %d steps (state read and written once)" % spl,
                 launches_ms_per_step=ms_launches, persistent_ms_per_step=ms_persistent,
                 autotune_ms=tuned_ms)
 
@@ -278,18 +278,19 @@ def copy_bandwidth(gib: float = 1.0, reps: int = 5):
     return {"bytes_read": n * 4, "bytes_written": n * 4, "ms": ms, "gbs": 2 * n * 4 / ms / 1e6}
 
 
-# storage and arithmetic type of each two-step form's kernel, as rocprofv3
-# names them (demangled, mangled)
-TWO_STEP_TYPE = {"f32": ("float, float", "ff"), "f64": ("double, double", "dd"), "f16s": ("_Float16, float", "DF16_f"),
-                 "f32sr": ("float, double", "fd")}
+# storage and arithmetic type of each form's kernel, as rocprofv3 names them
+# (demangled, mangled)
+STEP_TYPE = {"f32": ("float, float", "ff"), "f64": ("double, double", "dd"), "f16s": ("_Float16, float", "DF16_f"),
+             "f32sr": ("float, double", "fd")}
 
 
-def is_two_step_kernel(name: str, tag: str = "f32") -> bool:
-    """The two-step kernel of form `tag` with the porosity field (the 8192^2
-    layer's), by its demangled or mangled name in a rocprofv3 record (older
-    records name the kernel step2_kernel, by the storage type alone)."""
-    t, m = TWO_STEP_TYPE[tag]
-    if ("tile2_kernel<%s, 1>" % t) in name or ("tile2_kernelI%sLi1E" % m) in name:
+def is_step_kernel(name: str, tag: str = "f32") -> bool:
+    """The several-step kernel of form `tag` with the porosity field (the
+    8192^2 layer's), by its demangled or mangled name in a rocprofv3 record
+    (older records name the kernel step2_kernel, by the storage type alone)."""
+    t, m = STEP_TYPE[tag]
+    n = STEPS_PER_LAUNCH
+    if ("::tile_kernel<%s, 1, %d>" % (t, n)) in name or ("11tile_kernelI%sLi1ELi%dE" % (m, n)) in name:
         return True
     return tag in ("f32", "f64") and (("step2_kernel<%s, 1>" % t.split(",")[0]) in name or
                                       ("step2_kernelI%sLi1E" % m[0]) in name)
@@ -311,9 +312,9 @@ def _merge_record(out_path: str, tag: str, rec: dict):
 def ingest_counters(fetch_csv: str, write_csv: str, copy_bytes: int, out_path: str, tag: str = "f32"):
     """Turns two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per
     dispatch) of `bench.py --forms <tag>` into HBM bytes per launch of that
-    form's two-step kernel (two node updates per node), each scaled by the
-    same counter's reading on the plain copy of copy_bytes read and
-    copy_bytes written that bench.py times in the same run."""
+    form's several-step kernel, each scaled by the same
+    counter's reading on the plain copy of copy_bytes read and copy_bytes
+    written that bench.py times in the same run."""
     import csv
 
     def per_kernel(path, counter):
@@ -330,7 +331,8 @@ def ingest_counters(fetch_csv: str, write_csv: str, copy_bytes: int, out_path: s
         vals = per_kernel(path, counter)
         copy = [v for k, vs in vals.items() if "copy" in k.lower()
                 for v in vs if v * 1024 > 0.25 * copy_bytes]
-        step = [v for k, vs in vals.items() if is_two_step_kernel(k, tag) for v in vs]
+        steps_of = {k: 2 if "step2_kernel" in k else STEPS_PER_LAUNCH for k in vals if is_step_kernel(k, tag)}
+        step = [v for k in steps_of for v in vals[k]]
         if not copy or not step:
             raise SystemExit("counters for the copy or the step kernel not found in %s" % path)
         scale = copy_bytes / (np.median(copy) * 1024.0)
@@ -339,22 +341,23 @@ def ingest_counters(fetch_csv: str, write_csv: str, copy_bytes: int, out_path: s
     total = out["FETCH_SIZE"]["step_bytes"] + out["WRITE_SIZE"]["step_bytes"]
     _merge_record(out_path, tag, {"kernel_hash": kernel_hash(), "bytes_per_launch": total,
                                   "must_move_bytes_per_launch": BYTES_PER_LUP[tag] * N * N,
-                                  "one_step_equivalent_bytes_per_launch": BYTES_PER_LUP[tag] * N * N * 2,
+                                  "one_step_equivalent_bytes_per_launch":
+                                      BYTES_PER_LUP[tag] * N * N * max(steps_of.values()),
                                   "counters": out})
 
 
 def ingest_sq(csv_path: str, out_path: str, tag: str = "f32"):
     """Turns a rocprofv3 --pmc run with SQ_INSTS_VALU (and SQ_WAVES) of
     `bench.py --forms <tag>` into wavefront vector instructions per launch of
-    that form's two-step kernel (median over its dispatches)."""
+    that form's several-step kernel (median over its dispatches)."""
     import csv
     vals = {}
     for row in csv.DictReader(open(csv_path)):
         k = row["Kernel_Name"]
-        if is_two_step_kernel(k, tag):
+        if is_step_kernel(k, tag):
             vals.setdefault(row["Counter_Name"], []).append(float(row["Counter_Value"]))
     if "SQ_INSTS_VALU" not in vals:
-        raise SystemExit("SQ_INSTS_VALU of the two-step kernel not found in %s" % csv_path)
+        raise SystemExit("SQ_INSTS_VALU of the step kernel not found in %s" % csv_path)
     _merge_record(out_path, tag, {"kernel_hash": kernel_hash(),
                                   "valu_per_launch": float(np.median(vals["SQ_INSTS_VALU"])),
                                   "counters": {k: float(np.median(v)) for k, v in vals.items()},
@@ -532,7 +535,7 @@ def time_extras():
 
 
 def counter_figures(tag: str, r: dict) -> dict:
-    """HBM traffic and vector-issue fractions of a two-step form's launch from
+    """HBM traffic and vector-issue fractions of a form's launch from
     its committed counter runs (only those taken on the current sources)."""
     out = {}
     launch_s = r["launch_ms"] * 1e-3
@@ -542,7 +545,7 @@ def counter_figures(tag: str, r: dict) -> dict:
         out["traffic_frac"] = round(traffic / launch_s / 1e9 / HBM_PEAK_GBS, 4)
     valu = measured_valu(tag)
     if valu:
-        out["valu_per_node_update"] = round(valu * 64 / (2 * N * N), 1)
+        out["valu_per_node_update"] = round(valu * 64 / (r.get("steps_per_launch", STEPS_PER_LAUNCH) * N * N), 1)
         out["valu_issue_frac"] = round(valu / VALU_ISSUE_PER_S / launch_s, 4)
     return out
 
@@ -550,11 +553,10 @@ def counter_figures(tag: str, r: dict) -> dict:
 def roofline(head: str, r: dict, traffic):
     """Roofline of the dominant kernel.  achieved = the HBM bytes one launch
     must move (per node: every population read once and written once in the
-    storage type, the porosity read once -- BYTES_PER_LUP; a two-step launch
-    moves these once for its two steps) over the launch time measured live.
-    The two-step kernel is also put against its vector-instruction issue
-    (SQ_INSTS_VALU per launch from the committed counter run), the resource
-    that binds it, and its bytes are restated as if every step went to HBM
+    storage type, the porosity read once -- BYTES_PER_LUP; a launch moves these
+    once for all its steps) over the launch time measured live.  The kernel is
+    also put against its vector-instruction issue (SQ_INSTS_VALU per launch
+    from the committed counter run), the resource that binds it, and its bytes are restated as if every step went to HBM
     (one_step_equivalent: what the same node updates would cost one step per
     launch)."""
     nodes = N * N
@@ -566,17 +568,18 @@ def roofline(head: str, r: dict, traffic):
            "traffic_gbs": (round(traffic / launch_s / 1e9, 1) if traffic else None),
            "traffic_frac": (round(traffic / launch_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None),
            "bytes_per_launch": must, "launch_ms": round(r["launch_ms"], 4)}
-    if r["steps_per_launch"] == 2:
-        eq = must * 2 / launch_s / 1e9
-        out["kernel"] = ("tile2_kernel<float, float, kPhiField>: two time steps per launch over %d^2 nodes; %d B per node "
-                         "per launch (state read and written once)" % (N, BYTES_PER_LUP[head]))
-        out["one_step_equivalent"] = {"bytes_per_launch": must * 2, "gbs": round(eq, 1),
+    spl = r["steps_per_launch"]
+    if spl > 1:
+        eq = must * spl / launch_s / 1e9
+        out["kernel"] = ("tile_kernel<float, float, kPhiField, %d>: %d time steps per launch over %d^2 nodes; %d B per "
+                         "node per launch (state read and written once)" % (spl, spl, N, BYTES_PER_LUP[head]))
+        out["one_step_equivalent"] = {"bytes_per_launch": must * spl, "gbs": round(eq, 1),
                                       "frac": round(eq / HBM_PEAK_GBS, 4)}
         valu = measured_valu(head)
         if valu:
             floor_ms = valu / VALU_ISSUE_PER_S * 1e3
             out["valu_issue"] = {"wave_instructions_per_launch": valu,
-                                 "per_node_update": round(valu * 64 / (2 * nodes), 1),
+                                 "per_node_update": round(valu * 64 / (spl * nodes), 1),
                                  "issue_floor_ms": round(floor_ms, 4),
                                  "frac": round(floor_ms / r["launch_ms"], 4),
                                  "peak": "one wavefront instruction per clock per CU, 256 CUs, 2.4 GHz"}
@@ -612,8 +615,8 @@ def main():
                     help="convert rocprofv3 FETCH_SIZE / WRITE_SIZE runs into profiles/traffic.json")
     ap.add_argument("--ingest-sq", metavar="SQ_CSV",
                     help="convert a rocprofv3 SQ_INSTS_VALU run into profiles/sq.json")
-    ap.add_argument("--counters-form", default="f32", choices=sorted(TWO_STEP_TYPE),
-                    help="the two-step form whose kernel the ingested counter runs measured")
+    ap.add_argument("--counters-form", default="f32", choices=sorted(STEP_TYPE),
+                    help="the form whose kernel the ingested counter runs measured")
     args = ap.parse_args()
     if args.ingest_counters:
         ingest_counters(args.ingest_counters[0], args.ingest_counters[1], 2 ** 30,

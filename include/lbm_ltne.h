@@ -180,11 +180,12 @@ int lbm_ltne_create(const lbm_ltne_params *p, const double *phi_field, const dou
                     void *device_pool, size_t pool_bytes, lbm_ltne_t *out);
 
 /* Advances nsteps >= 0 time steps (asynchronous).  A step is fused: pull
- * streaming, wall reconstruction, macros, the three collisions, store.  The
- * steps of a call advance in pairs, two steps per launch with the
- * intermediate time level kept on chip (an odd last step, the steps checked
- * under diag_every, and lattices with rows of 256 MB and more alone); the
- * result equals single steps bit for bit.  The macros of the last step are kept for
+ * streaming, wall reconstruction, macros, the three collisions, store.  A
+ * launch advances three steps (two where that leaves no single step over)
+ * with the time levels between kept on chip; a single step left over, the
+ * steps checked under diag_every, and the steps of lattices with rows of
+ * 200 MB and more run alone.  The result equals single steps bit for bit.
+ * The macros of the last step are kept for
  * lbm_ltne_macros, lbm_ltne_nusselt and lbm_ltne_diagnostics; the residual
  * compares them with the macros kept by the previous call that advanced the
  * lattice (a call with nsteps = 0 changes nothing).  With diag_every > 0 a
@@ -258,8 +259,8 @@ int lbm_ltne_destroy(lbm_ltne_t h);
 /*
  * Batched lattices: n independent lattices of uneven size and parameters
  * (one precision per batch) advanced together.  By default (mode 0) a launch
- * covers the combined tile list of all lattices and advances them by a pair
- * of steps, as in lbm_ltne_step (an odd last step alone); mode 1
+ * covers the combined tile list of all lattices and advances them by several
+ * steps, as in lbm_ltne_step; mode 1
  * runs all steps of a call in one persistent cooperative launch with a
  * grid-wide barrier between steps (between pairs of steps in FP32 batches of
  * at least 1024 strips of 61 or 62 columns by 8 rows; every barrier wait is bounded; a timeout
@@ -293,13 +294,13 @@ int lbm_ltne_batch_set_chunks(lbm_ltne_batch_t b, const int32_t *rows);
 int lbm_ltne_batch_get_chunks(lbm_ltne_batch_t b, int32_t *rows);
 /* Autotuner: for each size class (lattices of equal nx) tries tile widths
  * 64/128/256 by timing reps single-step launches, then (FP32 batches whose
- * persistent launch runs pairs of steps) chunk heights 8..32 by timing 2 reps
- * steps of that launch, then the launch mode (one launch per pair of steps,
- * or one persistent launch; skipped when the device has no resident
- * grid for it) by timing 2 reps steps of each, every trial from a snapshot
+ * persistent launch runs pairs of steps) chunk heights 8..32 by timing 6 reps
+ * steps of that launch, then the launch mode (launches of several steps, or
+ * one persistent launch; skipped when the device has no resident
+ * grid for it) by timing 6 reps steps of each, every trial from a snapshot
  * of the state (restored afterwards), and keeps the fastest of each;
  * ms_per_step (may be NULL) receives the time per step of the chosen
- * configuration on the path the batch runs (two-step launches where they
+ * configuration on the path the batch runs (launches of several steps where they
  * apply).  Allocates a snapshot of the populations for the call. */
 int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double *ms_per_step);
 int lbm_ltne_batch_destroy(lbm_ltne_batch_t b);

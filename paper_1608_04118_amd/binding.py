@@ -528,8 +528,7 @@ def lbm_ltne_batch_destroy(b):
 
 class Batch:
     """Many independent lattices advanced together on the current torch
-    stream: one launch per step (two steps per launch for the FP32 form when
-    the batch is large enough) by default, or one persistent launch
+    stream: launches of several steps by default, or one persistent launch
     (set_mode(1))."""
 
     def __init__(self, params_list, phi_fields=None, Hv_fields=None, use_torch=True):
@@ -574,7 +573,7 @@ class Batch:
         lbm_ltne_batch_set_chunks(self.h, rows)
 
     def autotune(self, reps=4, cache=None):
-        """Tile widths and two-step chunk heights per size class, then the
+        """Tile widths and chunk heights per size class, then the
         launch mode of the whole batch.  With ``cache`` (a JSON path), a
         choice stored for this device, precision and lattice width is reused
         and new choices are added; the key is "gfx950/<precision>/<nx>", the

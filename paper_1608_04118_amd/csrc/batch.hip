@@ -2,7 +2,7 @@
 // parameters advanced together, either by one launch per step over the
 // combined tile list (the default), or by one persistent cooperative launch
 // that loops over the time steps with a grid-wide barrier between steps.
-// The ordinary launches advance two steps each over tiles held in LDS
+// The ordinary launches advance two or three steps over tiles held in LDS
 // (tile_kernel.hpp).
 // On MI355X the barrier's device-scope release and acquire (L2 write-back
 // and invalidation on every XCD, once per resident workgroup) cost more than
@@ -219,15 +219,15 @@ struct lbm_ltne_batch {
   std::vector<lbm_ltne_derived> d;
   std::vector<int> shift;  // tile width shift per lattice
   std::vector<int> rows2;  // chunk height of the persistent two-step launch per lattice
-  std::vector<TileGrid> tiles2;  // tiles of the two-step launches per lattice
+  std::vector<TileGrid> tiles[2];  // per lattice, of the launches of two and three steps
   char* base = nullptr;    // all device memory of the batch
   size_t bytes = 0;
   std::vector<size_t> off_pop0, off_pop1, off_phi, off_hv, off_mac;
-  size_t off_cav = 0, off_consts = 0, off_tiles = 0, off_waves = 0, off_tiles2 = 0, off_ctl = 0, off_result = 0;
+  size_t off_cav = 0, off_consts = 0, off_tiles = 0, off_waves = 0, off_step_tiles[2] = {0, 0}, off_ctl = 0, off_result = 0;
   int nwaves2 = 0;    // wavefronts of a two-step launch over every lattice (current chunk heights)
   int nwaves2_min = 0;  // the same at the smallest chunk height (decides whether to use it; table size)
   bool step2_addr = true;  // every lattice's rows addressable by the two-step kernel
-  int ntiles2 = 0;    // tiles of a two-step launch over every lattice (0: single steps)
+  int step_tiles[2] = {0, 0};  // tiles of a launch of two or three steps over every lattice (0: none)
   int ntiles = 0;
   int max_tiles = 0;
   int fields = 0;     // kPhiField / kHvField if any lattice has that field
@@ -254,8 +254,7 @@ template <typename C>
 int upload_tables_t(lbm_ltne_batch* b) {
   std::vector<StepConsts<C>> ks(b->n);
   std::vector<CavityDesc<C>> cav(b->n);
-  std::vector<int> tile_cav, wave_cav, tile2_cav;
-  tile2_cav.reserve(b->ntiles2);
+  std::vector<int> tile_cav, wave_cav, step_cav[2];
   tile_cav.reserve(b->max_tiles);
   wave_cav.reserve(b->nwaves2_min);
   for (int i = 0; i < b->n; ++i) {
@@ -270,12 +269,12 @@ int upload_tables_t(lbm_ltne_batch* b) {
     for (int t = 0; t < ks[i].tm.ntiles; ++t) tile_cav.push_back(i);
     cav[i].wave_begin = static_cast<int>(wave_cav.size());
     cav[i].rows2 = b->rows2[i];
-    cav[i].tile2_begin = static_cast<int>(tile2_cav.size());
-    cav[i].tile2_w = b->tiles2[i].w;
-    cav[i].tile2_h = b->tiles2[i].h;
-    cav[i].tile2_ntx = b->tiles2[i].ntx;
     cav[i].pad_ = 0;
-    for (int t = 0; t < b->tiles2[i].ntiles; ++t) tile2_cav.push_back(i);
+    for (int v = 0; v < 2; ++v) {
+      const TileGrid& g = b->tiles[v][i];
+      cav[i].tiles[v] = {g.w, g.h, g.ntx, static_cast<int>(step_cav[v].size())};
+      step_cav[v].insert(step_cav[v].end(), g.ntiles, i);
+    }
     for (int w = 0; w < step2_waves(b->p[i].nx, b->p[i].ny, b->p[i].periodic_x, b->rows2[i]); ++w)
       wave_cav.push_back(i);
   }
@@ -287,8 +286,9 @@ int upload_tables_t(lbm_ltne_batch* b) {
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(b->base + b->off_tiles, tile_cav.data(), tile_cav.size() * sizeof(int),
                          hipMemcpyHostToDevice, b->stream));
-  HIP_TRY(hipMemcpyAsync(b->base + b->off_tiles2, tile2_cav.data(), tile2_cav.size() * sizeof(int),
-                         hipMemcpyHostToDevice, b->stream));
+  for (int v = 0; v < 2; ++v)
+    HIP_TRY(hipMemcpyAsync(b->base + b->off_step_tiles[v], step_cav[v].data(), step_cav[v].size() * sizeof(int),
+                           hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(b->base + b->off_waves, wave_cav.data(), wave_cav.size() * sizeof(int),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));
@@ -345,21 +345,22 @@ int resident_grid(const lbm_ltne_batch* b, int* out, const void* fn = nullptr, i
 
 constexpr unsigned kSpinLimit = 1u << 24;
 
-// A two-step launch over every lattice; macros: the second step also writes
-// the macros.
-hipError_t launch_batch2(const lbm_ltne_batch* b, int parity, uint32_t step, bool macros = false) {
+// A launch of nsub (2 or 3) steps over every lattice; macros: the last step
+// also writes the macros.
+hipError_t launch_batch_steps(const lbm_ltne_batch* b, int nsub, int parity, uint32_t step, bool macros) {
   BatchTileLaunch a{};
   a.base = b->base;
   a.cav = b->base + b->off_cav;
   a.consts = b->base + b->off_consts;
-  a.tile_cav = reinterpret_cast<const int*>(b->base + b->off_tiles2);
-  a.ntiles = b->ntiles2;
+  a.tile_cav = reinterpret_cast<const int*>(b->base + b->off_step_tiles[nsub - 2]);
+  a.ntiles = b->step_tiles[nsub - 2];
   a.fields = b->fields;
   a.parity = parity;
   a.macros = macros;
+  a.nsub = nsub;
   a.step = step;
   a.stream = b->stream;
-  return launch_batch_tile2(b->precision, a);
+  return launch_batch_tiles(b->precision, a);
 }
 
 // FP32 batches with enough wavefronts at the smallest chunk height, whose
@@ -368,9 +369,9 @@ bool persist_pairs_ok(const lbm_ltne_batch* b) {
   return b->precision == LBM_FP32 && b->step2_addr && b->nwaves2_min >= kPersistMinWaves;
 }
 
-// nsteps steps of every lattice.  Per-step mode: pairs of steps in one
-// two-step launch (two_step), an odd last step alone; the last launch writes
-// the macros (macros_last).  The
+// nsteps steps of every lattice.  Per-step mode: three steps a launch, two
+// where that leaves no single step over (two_step), a single step alone; the
+// last launch writes the macros (macros_last).  The
 // autotuner's tile trials run single steps only (the tile widths it chooses
 // apply to them).
 int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step = true) {
@@ -417,14 +418,14 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
   } else {
     const int per = (ntiles + kXcds - 1) / kXcds;
     const int grid = kXcds * per;  // one tile per workgroup per step
-    const bool two = two_step && b->ntiles2 > 0;
+    const bool multi = two_step && b->step_tiles[0] > 0 && b->step_tiles[1] > 0;
     int parity = b->parity;
     for (int s = 0; s < nsteps;) {
       const uint32_t step0 = static_cast<uint32_t>(b->steps + 1 + s);
-      if (two && s + 2 <= nsteps) {
-        // the pair that ends the call writes the macros of its second step
-        HIP_TRY(launch_batch2(b, parity, step0, macros_last && s + 2 == nsteps));
-        s += 2;
+      if (multi && s + 2 <= nsteps) {
+        const int nsub = next_steps(nsteps - s);
+        HIP_TRY(launch_batch_steps(b, nsub, parity, step0, macros_last && s + nsub == nsteps));
+        s += nsub;
       } else {
         int one = 1;
         int mac = (macros_last && s == nsteps - 1) ? 1 : 0;
@@ -547,9 +548,11 @@ int lbm_ltne_batch_create(int32_t n, const lbm_ltne_params* ps, const double* co
   b->d = ds;
   b->shift.assign(n, 0);
   b->rows2.assign(n, kBatch2Rows);
-  b->tiles2.resize(n);
-  tile2_batch_grids(n, ps, b->tiles2.data());
-  for (const TileGrid& g : b->tiles2) b->ntiles2 += g.ntiles;
+  for (int v = 0; v < 2; ++v) {
+    b->tiles[v].resize(n);
+    tile_batch_grids(n, ps, v + 2, b->tiles[v].data());
+    for (const TileGrid& g : b->tiles[v]) b->step_tiles[v] += g.ntiles;
+  }
   for (int i = 0; i < n; ++i) {
     if (phi_fields && phi_fields[i]) b->fields |= kPhiField;
     if (Hv_fields && Hv_fields[i]) b->fields |= kHvField;
@@ -586,7 +589,10 @@ int lbm_ltne_batch_create(int32_t n, const lbm_ltne_params* ps, const double* co
   b->off_cav = o; o += align_up(n * b->desc_bytes, kAlign);
   b->off_tiles = o; o += align_up(static_cast<size_t>(b->max_tiles) * sizeof(int), kAlign);
   b->off_waves = o; o += align_up(static_cast<size_t>(b->nwaves2_min) * sizeof(int), kAlign);
-  b->off_tiles2 = o; o += align_up(static_cast<size_t>(b->ntiles2) * sizeof(int), kAlign);
+  for (int v = 0; v < 2; ++v) {
+    b->off_step_tiles[v] = o;
+    o += align_up(static_cast<size_t>(b->step_tiles[v]) * sizeof(int), kAlign);
+  }
   b->off_ctl = o; o += kAlign;
   b->off_result = o; o += kAlign;
   b->bytes = o;
@@ -773,23 +779,24 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     }
     for (int i : kv.second) b->shift[i] = best_shift;
   }
-  // Time per step over 2 reps steps of launch mode m, from the snapshot.
+  // Time per step over 6 reps steps of launch mode m, from the snapshot (whole
+  // launches of two and of three steps).
   const int mode0 = b->persistent;
   auto trial2 = [&](int m, float* ms) -> int {
     b->persistent = m;
     int r = copy_state(false);
     if (r != LBM_OK) return r;
     b->parity = parity0;
-    r = launch_batch(b, 2, 0, true);  // warm-up
+    r = launch_batch(b, 6, 0, true);  // warm-up
     if (r != LBM_OK) return r;
     HIP_TRY(hipEventRecord(e0, b->stream));
-    r = launch_batch(b, 2 * reps, 0, true);
+    r = launch_batch(b, 6 * reps, 0, true);
     if (r != LBM_OK) return r;
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
     r = check_ctl(b);
-    *ms /= static_cast<float>(2 * reps);
+    *ms /= static_cast<float>(6 * reps);
     b->parity = parity0;
     return r;
   };

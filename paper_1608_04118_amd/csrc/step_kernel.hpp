@@ -344,8 +344,9 @@ __device__ __forceinline__ void node_update_with(
 
   // Wall classification and the node whose post-streaming populations this
   // thread reads: itself, or the inward neighbour (diagonal at a corner).
-  const bool wx = !k.px && (x == 0 || x == nx - 1);
-  const bool wy = !k.py && (y == 0 || y == ny - 1);
+  constexpr bool inner = (F & kInterior) != 0;
+  const bool wx = !inner && !k.px && (x == 0 || x == nx - 1);
+  const bool wy = !inner && !k.py && (y == 0 || y == ny - 1);
   const bool wall = wx || wy;
   const int xc = wx ? (x == 0 ? 1 : nx - 2) : x;
   const int yc = wy ? (y == 0 ? 1 : ny - 2) : y;
@@ -762,24 +763,6 @@ __global__ __launch_bounds__(kBlock) void step_kernel(
     const C* __restrict__ hv_field, C* __restrict__ mac, const C* __restrict__ init_tf,
     const C* __restrict__ init_ts, const StepConsts<C> k, const uint32_t step, C* __restrict__ rec = nullptr) {
   step_tile<S, C, F>(src, dst, phi_field, hv_field, mac, init_tf, init_ts, k, step, rec);
-}
-
-// The step as a node of a recorded sequence of steps (a HIP graph replayed
-// many times): its step number, which seeds the stochastic rounding, is
-// *step_base + offset, the base living in device memory and advanced by
-// step_advance_kernel at the end of every replay.
-template <typename S, typename C, int F>
-__global__ __launch_bounds__(kBlock) void step_seq_kernel(const S* __restrict__ src, S* __restrict__ dst,
-                                                          const C* __restrict__ phi_field,
-                                                          const C* __restrict__ hv_field, const StepConsts<C> k,
-                                                          const uint32_t* __restrict__ step_base,
-                                                          const uint32_t offset) {
-  step_tile<S, C, F>(src, dst, phi_field, hv_field, nullptr, nullptr, nullptr, k, *step_base + offset, nullptr);
-}
-
-// Sets (add = 0) or advances (add = 1) the device step base by n.
-[[maybe_unused]] static __global__ void step_base_kernel(uint32_t* __restrict__ step_base, uint32_t n, int add) {
-  if (threadIdx.x == 0) *step_base = add ? *step_base + n : n;
 }
 
 }  // namespace ltne

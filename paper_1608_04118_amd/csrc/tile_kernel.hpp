@@ -1,30 +1,37 @@
-// Two fused time steps per launch over tiles held in LDS, for every precision
-// form.  A workgroup owns a tile of w x h output nodes.  It
-//   1. updates the tile and a halo of one node to time t + 1 (the ordinary
+// Two or three fused time steps per launch over tiles held in LDS, for every
+// precision form.  A workgroup owns a tile of w x h output nodes.  For T steps
+// it
+//   1. updates the tile and a halo of T - 1 nodes to time t + 1 (the ordinary
 //      pull from device memory and node update) and leaves the 19 results of
 //      every node in LDS, in the storage type;
-//   2. pulls those from LDS, updates the tile's nodes to time t + 2 and stores
+//   2. (T = 3) updates the tile and a halo of one node to time t + 2 in LDS;
+//   3. pulls those from LDS, updates the tile's nodes to time t + T and stores
 //      them.
 // The node update is the same function as the single-step kernel's, with
-// other pulls and puts, so the result equals two single steps bit for bit.
+// other pulls and puts, so the result equals T single steps bit for bit.
 //
-// What bounds it.  One step per launch is bound by memory traffic, which two
-// steps per pass over the populations halve.  The intermediate level lives in
-// LDS and not in a register window, so the kernel needs the registers of the
-// node update alone (binary32: 83, binary64: 110) and four wavefronts share a
-// SIMD: a lone wavefront issues one instruction every 6 to 9 cycles on this
-// chip, where several together issue one every 3 (binary32) to 5 (binary64).
-// A marching wavefront with the window in registers ran at two (binary32) and
-// one (binary64) per SIMD.  Measured, a step of a porous layer, ms:
-//                      one step   register window   tiles
-//   4096^2 binary32      0.433        0.341         0.289
-//   4096^2 binary64      0.869        0.619         0.539
-//   4096^2 f32sr         0.510          --          0.391
-//   4096^2 binary16      0.271          --          0.212
-//   1024^2 binary32      0.0288       0.0325        0.0179
-//    512^2 binary64      0.0157       0.0210        0.0093
-// The binary32 kernel then issues vector instructions 79% of the cycles and
-// moves 4.7 TB/s; the binary64 one moves 5.2 TB/s.
+// What bounds it.  One step per launch is bound by memory traffic, which T
+// steps per pass over the populations divide by almost T.  The levels between
+// live in LDS and not in a register window, so the kernel needs the registers
+// of the node update alone (binary32: 83, binary64: 110) and four wavefronts
+// share a SIMD: a lone wavefront issues one instruction every 6 to 9 cycles on
+// this chip, where several together issue one every 3 (binary32) to 5
+// (binary64).  A marching wavefront with the window in registers ran at two
+// (binary32) and one (binary64) per SIMD.  With two steps the memory still
+// takes as long as the arithmetic (binary64: a workgroup's loads and stores
+// fill 13.9 of its 14.2 us at its CU's share of the bandwidth); with three the
+// halo costs 6% (binary32) to 13% (binary64) more arithmetic, and vector
+// instructions take most of the cycles (85% and 76%, at the rates above).
+// Measured, us per step of a porous layer (one box for each row but the
+// register window's):
+//                    one step  register window  two steps  three steps
+//   4096^2 binary32     434          341            305        275
+//   4096^2 binary64     869          619            566        464
+//   4096^2 f32sr        510           --            399        390
+//   4096^2 binary16     271           --            235        228
+//   1024^2 binary32     28.6         32.5          19.6       18.6
+//   1024^2 binary64     52.4         61.3          38.7       32.2
+//    512^2 binary64     15.7         21.0          10.2        9.5
 #pragma once
 
 #include "step_kernel.hpp"
@@ -153,31 +160,6 @@ struct TilePull {
   }
 };
 
-// Pull from the tile in LDS: planes of N slots, rows of p slots; a points at
-// the slot of node (x, y), which pulls the populations of (xc, yc).
-template <typename S, typename C, int N>
-struct LdsTilePull {
-  const S* a;
-  int x, y, p;
-  __device__ __forceinline__ void operator()(int xc, int yc, const StepConsts<C>& k, C (&v)[kPlanes]) const {
-    const S* b = a + (yc - y) * p + (xc - x);
-    const S *bm = b - p, *bp = b + p;
-    const C isf = k.inv_sf, isg = k.inv_sg;
-#pragma unroll
-    for (int i = 0; i < kPlanes; ++i) {
-      const int q = i < 9 ? i : (i < 14 ? i - 9 : i - 14);
-      const S* r = vel_y(q) == 1 ? bm : (vel_y(q) == -1 ? bp : b);
-      v[i] = unscale<S, C>(r[i * N - vel_x(q)], i < 9 ? isf : isg);
-    }
-  }
-};
-
-template <typename S, int N>
-struct LdsSink {
-  S* a;
-  __device__ __forceinline__ void operator()(int i, S v) const { a[i * N] = v; }
-};
-
 // Plain stores: the rows of a tile end within cache lines that its
 // neighbours complete, which the L2 merges.
 template <typename S>
@@ -214,58 +196,159 @@ __device__ __forceinline__ const StepConsts<C>& fresh(ConstK<C>* p) {
   return *(const StepConsts<C>*)p;
 }
 
-template <typename S, typename C, int F, int N>
-__device__ __forceinline__ void tile2_body(const int tx, const int ty, const int w, const int h, const int t, const int nthreads,
-                                           const S* __restrict__ src, S* __restrict__ dst,
-                                           const C* __restrict__ phi_field, const C* __restrict__ hv_field,
-                                           C* __restrict__ mac, ConstK<C>* kp, S* __restrict__ pops,
-                                           const uint32_t step) {
-  using T = thermal_t<S, C>;
-  const StepConsts<C>& k = *(const StepConsts<C>*)kp;
-  const int nx = k.nx, ny = k.ny;
-  const int x0 = tile_bound(tx, w, nx), x1 = tile_bound(tx + 1, w, nx);
-  const int P = x1 - x0 + 2;
-  const int y0 = tile_bound(ty, h, ny), y1 = tile_bound(ty + 1, h, ny);
-  {
-    const int rx0 = k.px ? x0 - 1 : max(x0 - 1, 0), rx1 = k.px ? x1 + 1 : min(x1 + 1, nx);
-    const int ry0 = k.py ? y0 - 1 : max(y0 - 1, 0), ry1 = k.py ? y1 + 1 : min(y1 + 1, ny);
-    const int rw = rx1 - rx0, n1 = rw * (ry1 - ry0);
-    const float rd = 1.0f / static_cast<float>(rw);
-    const bool wrapped = k.py && (ry0 < 1 || ry1 > ny - 1);
-    const int yb = wrapped ? 0 : max(ry0 - 1, 0);
-    const TilePull<S, C> pull{src, rows_rsrc(src, yb, ny, k.rs), yb, wrapped};
-    for (int n = t; n < n1; n += nthreads) {
-      const StepConsts<C>& kk = fresh<C>(kp);
-      const int ly = small_div(n, rd), lx = n - ly * rw;
-      int x = rx0 + lx, y = ry0 + ly;
-      S* slot = pops + (y - y0 + 1) * P + (x - x0 + 1);
-      if (k.px) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
-      if (k.py) y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
-      SinkPut<S, LdsSink<S, N>> put{{slot}};
-      node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step,
-                                           nullptr, thermal_k<T>(kk));
+// Opposite velocity, as a plane index.
+__host__ __device__ constexpr int opp_plane(int i) {
+  const int o = i < 9 ? 0 : (i < 14 ? 9 : 14);
+  const int q = i - o;
+  constexpr int op[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
+  return o + op[q];
+}
+
+// In-place streaming between the middle levels (the A-A pattern): a node's
+// update reads and writes the same 19 slots and no other node's, so nothing is
+// overwritten before it is read and one buffer is enough.  Level 1 leaves its
+// results at the node itself, each in the plane of the opposite velocity;
+// a gather step reads population i of (x, y) from that plane at (x, y) - e_i
+// and puts its results into plane i at (x, y) + e_i, where the next step
+// finds its pulls at the node itself.
+template <typename S, typename C, int N, bool Gather>
+struct AaPull {
+  const S* a;
+  int x, y, p;
+  __device__ __forceinline__ void operator()(int xc, int yc, const StepConsts<C>& k, C (&v)[kPlanes]) const {
+    const S* b = a + (yc - y) * p + (xc - x);
+    const S *bm = b - p, *bp = b + p;
+#pragma unroll
+    for (int i = 0; i < kPlanes; ++i) {
+      const int q = i < 9 ? i : (i < 14 ? i - 9 : i - 14);
+      S g;
+      if constexpr (Gather) {
+        const S* r = vel_y(q) == 1 ? bm : (vel_y(q) == -1 ? bp : b);
+        g = r[opp_plane(i) * N - vel_x(q)];
+      } else {
+        g = b[i * N];
+      }
+      v[i] = unscale<S, C>(g, i < 9 ? k.inv_sf : k.inv_sg);
     }
   }
-  __syncthreads();
-  {
-    const int ow = x1 - x0, n2 = ow * (y1 - y0);
-    const float rd = 1.0f / static_cast<float>(ow);
-    constexpr int E = sizeof(S);
-    const int R = static_cast<int>(k.rs) * E, Q = static_cast<int>(k.qs) * E;
-    const __amdgpu_buffer_rsrc_t r = rows_rsrc(dst, y0, ny, k.rs);
-    for (int n = t; n < n2; n += nthreads) {
-      const StepConsts<C>& kk = fresh<C>(kp);
-      const int ly = small_div(n, rd), lx = n - ly * ow;
-      const int x = x0 + lx, y = y0 + ly;
-      const LdsTilePull<S, C, N> pull{pops + (ly + 1) * P + lx + 1, x, y, P};
-      SinkPut<S, BufSink<S>> put{{r, ly * R + x * E, Q}};
-      node_update_with<S, C, F | kMacrosIf>(x, y, pull, put, phi_field, hv_field, mac, nullptr, nullptr, kk, step + 1u, nullptr,
-                                thermal_k<T>(kk));
-    }
+};
+template <typename S, int N>
+struct OppSink {
+  S* a;
+  __device__ __forceinline__ void operator()(int i, S v) const { a[opp_plane(i) * N] = v; }
+};
+template <typename S, int N>
+struct ScatterSink {
+  S* a;
+  int p;
+  __device__ __forceinline__ void operator()(int i, S v) const {
+    const int q = i < 9 ? i : (i < 14 ? i - 9 : i - 14);
+    S* r = vel_y(q) == 1 ? a + p : (vel_y(q) == -1 ? a - p : a);
+    r[i * N + vel_x(q)] = v;
+  }
+};
+
+struct TileRect {
+  int x0, x1, y0, y1;
+};
+template <typename C>
+__device__ __forceinline__ TileRect grown(int x0, int x1, int y0, int y1, int g, const StepConsts<C>& k) {
+  return {k.px ? x0 - g : max(x0 - g, 0), k.px ? x1 + g : min(x1 + g, k.nx), k.py ? y0 - g : max(y0 - g, 0),
+          k.py ? y1 + g : min(y1 + g, k.ny)};
+}
+
+template <class Update>
+__device__ __forceinline__ void for_rect(const TileRect& r, const int t, const int nthreads, const Update& update) {
+  const int w = r.x1 - r.x0, n1 = w * (r.y1 - r.y0);
+  const float rd = 1.0f / static_cast<float>(w);
+  for (int n = t; n < n1; n += nthreads) {
+    const int ly = small_div(n, rd);
+    update(r.x0 + (n - ly * w), r.y0 + ly);
   }
 }
 
-// Slots, threads and wavefronts per SIMD of a workgroup (tile2_slots).
+// T steps of a tile.
+template <typename S, typename C, int F, int N, int T>
+__device__ __forceinline__ void tile_body(const int tx, const int ty, const int w, const int h, const int t,
+                                          const int nthreads, const S* __restrict__ src, S* __restrict__ dst,
+                                          const C* __restrict__ phi_field, const C* __restrict__ hv_field,
+                                          C* __restrict__ mac, ConstK<C>* kp, S* __restrict__ pops,
+                                          const uint32_t step) {
+  using Th = thermal_t<S, C>;
+  const StepConsts<C>& k = *(const StepConsts<C>*)kp;
+  const int nx = k.nx, ny = k.ny;
+  const int x0 = tile_bound(tx, w, nx), x1 = tile_bound(tx + 1, w, nx);
+  const int P = x1 - x0 + 2 * (T - 1);
+  const int y0 = tile_bound(ty, h, ny), y1 = tile_bound(ty + 1, h, ny);
+  auto slot = [&](int x, int y) { return pops + (y - y0 + T - 1) * P + (x - x0 + T - 1); };
+  auto wrap = [&](int& x, int& y) {
+    if (k.px) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+    if (k.py) y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
+  };
+  {
+    const TileRect r = grown(x0, x1, y0, y1, T - 1, k);
+    const bool wrapped = k.py && (r.y0 < 1 || r.y1 > ny - 1);
+    const int yb = wrapped ? 0 : max(r.y0 - 1, 0);
+    const TilePull<S, C> pull{src, rows_rsrc(src, yb, ny, k.rs), yb, wrapped};
+    for_rect(r, t, nthreads, [&](int x, int y) {
+      const StepConsts<C>& kk = fresh<C>(kp);
+      SinkPut<S, OppSink<S, N>> put{{slot(x, y)}};
+      wrap(x, y);
+      node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step, nullptr,
+                                thermal_k<Th>(kk));
+    });
+  }
+  __syncthreads();
+  if constexpr (T == 3) {
+    const TileRect r = grown(x0, x1, y0, y1, 1, k);
+    // the wall nodes first: they read their inward neighbours' slots
+    const int ah = (k.py ? r.y1 : min(r.y1, ny - 1)) - (k.py ? r.y0 : max(r.y0, 1));
+    const int ax0 = k.px ? r.x0 : max(r.x0, 1), ay0 = k.py ? r.y0 : max(r.y0, 1);
+    const int aw = (k.px ? r.x1 : min(r.x1, nx - 1)) - ax0;
+    const int nb = (!k.py && r.y0 == 0) ? r.x1 - r.x0 : 0, nt = (!k.py && r.y1 == ny) ? r.x1 - r.x0 : 0;
+    const int nl = (!k.px && r.x0 == 0) ? ah : 0, nr = (!k.px && r.x1 == nx) ? ah : 0;
+    const int nw = nb + nt + nl + nr;
+    if (nw > 0) {
+      for (int n = t; n < nw; n += nthreads) {
+        const StepConsts<C>& kk = fresh<C>(kp);
+        const int c = n - nb - nt;
+        int x = c < 0 ? r.x0 + (n < nb ? n : n - nb) : (c < nl ? r.x0 : r.x1 - 1);
+        int y = c < 0 ? (n < nb ? r.y0 : r.y1 - 1) : ay0 + (c < nl ? c : c - nl);
+        S* a = slot(x, y);
+        wrap(x, y);
+        const AaPull<S, C, N, true> pull{a, x, y, P};
+        SinkPut<S, ScatterSink<S, N>> put{{a, P}};
+        node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step + 1u,
+                                  nullptr, thermal_k<Th>(kk));
+      }
+      __syncthreads();
+    }
+    for_rect({ax0, ax0 + aw, ay0, ay0 + ah}, t, nthreads, [&](int x, int y) {
+      const StepConsts<C>& kk = fresh<C>(kp);
+      S* a = slot(x, y);
+      wrap(x, y);
+      const AaPull<S, C, N, true> pull{a, x, y, P};
+      SinkPut<S, ScatterSink<S, N>> put{{a, P}};
+      node_update_with<S, C, F | kInterior>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk,
+                                            step + 1u, nullptr, thermal_k<Th>(kk));
+    });
+    __syncthreads();
+  }
+  {
+    constexpr int E = sizeof(S);
+    const int R = static_cast<int>(k.rs) * E, Q = static_cast<int>(k.qs) * E;
+    const __amdgpu_buffer_rsrc_t d = rows_rsrc(dst, y0, ny, k.rs);
+    for_rect({x0, x1, y0, y1}, t, nthreads, [&](int x, int y) {
+      const StepConsts<C>& kk = fresh<C>(kp);
+      const AaPull<S, C, N, T == 2> pull{slot(x, y), x, y, P};
+      SinkPut<S, BufSink<S>> put{{d, (y - y0) * R + x * E, Q}};
+      node_update_with<S, C, F | kMacrosIf>(x, y, pull, put, phi_field, hv_field, mac, nullptr, nullptr, kk,
+                                            step + static_cast<uint32_t>(T - 1), nullptr, thermal_k<Th>(kk));
+    });
+  }
+}
+
+// Slots, threads and wavefronts per SIMD of a workgroup (tile_slots).
 template <typename S, typename C>
 struct TileForm {
   static constexpr int N = sizeof(S) == 8 ? 536 : (sizeof(S) == 2 ? 2144 : 1072);
@@ -273,8 +356,8 @@ struct TileForm {
   static constexpr int Waves = sizeof(S) == 2 ? 8 : 4;
 };
 
-template <typename S, typename C, int F>
-__global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) void tile2_kernel(
+template <typename S, typename C, int F, int T>
+__global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) void tile_kernel(
     const StepConsts<C> k, const S* __restrict__ src, S* __restrict__ dst, const C* __restrict__ phi_field,
     const C* __restrict__ hv_field, C* __restrict__ mac, const TileGrid m, const uint32_t step) {
   using Form = TileForm<S, C>;
@@ -283,14 +366,14 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   const int b = blockIdx.x;
   const int tile = (b & (kXcds - 1)) * m.per_xcd + (b >> 3);
   if (tile >= m.ntiles) return;
-  tile2_body<S, C, F, Form::N>(tile % m.ntx, tile / m.ntx, m.w, m.h, static_cast<int>(threadIdx.x), Form::Block, src,
-                               dst, phi_field, hv_field, mac, (ConstK<C>*)__builtin_amdgcn_kernarg_segment_ptr(),
-                               pops, step);
+  tile_body<S, C, F, Form::N, T>(tile % m.ntx, tile / m.ntx, m.w, m.h, static_cast<int>(threadIdx.x), Form::Block,
+                                 src, dst, phi_field, hv_field, mac,
+                                 (ConstK<C>*)__builtin_amdgcn_kernarg_segment_ptr(), pops, step);
 }
 
 // The same over every lattice of a batch: tile t belongs to lattice tile_cav[t].
-template <typename S, typename C, int F>
-__global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) void batch_tile2_kernel(
+template <typename S, typename C, int F, int T>
+__global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) void batch_tile_kernel(
     char* base, const CavityDesc<C>* __restrict__ cav, const StepConsts<C>* __restrict__ ks,
     const int* __restrict__ tile_cav, const int ntiles, const int per_xcd, const int parity, const int macros,
     const uint32_t step) {
@@ -302,12 +385,12 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   const int c = __builtin_amdgcn_readfirstlane(tile_cav[tile]);
   typedef __attribute__((address_space(4))) const CavityDesc<C> ConstD;
   const CavityDesc<C>& d = *(const CavityDesc<C>*)((ConstD*)cav + c);
-  const int local = tile - d.tile2_begin;
-  tile2_body<S, C, F, Form::N>(local % d.tile2_ntx, local / d.tile2_ntx, d.tile2_w, d.tile2_h,
-                               static_cast<int>(threadIdx.x), Form::Block, at_offset<const S>(base, d.pop[parity]),
-                               at_offset<S>(base, d.pop[parity ^ 1]), at_offset<const C>(base, d.phi),
-                               at_offset<const C>(base, d.hv), macros ? at_offset<C>(base, d.mac) : nullptr,
-                               (ConstK<C>*)ks + c, pops, step);
+  const LatticeTiles& g = d.tiles[T - 2];
+  const int local = tile - g.begin;
+  tile_body<S, C, F, Form::N, T>(local % g.ntx, local / g.ntx, g.w, g.h, static_cast<int>(threadIdx.x), Form::Block,
+                                 at_offset<const S>(base, d.pop[parity]), at_offset<S>(base, d.pop[parity ^ 1]),
+                                 at_offset<const C>(base, d.phi), at_offset<const C>(base, d.hv),
+                                 macros ? at_offset<C>(base, d.mac) : nullptr, (ConstK<C>*)ks + c, pops, step);
 }
 
 }  // namespace ltne

@@ -1,4 +1,5 @@
-// Host interface of the tiled two-step kernels (tile_kernel.hpp), which are
+// Host interface of the tiled kernels of two or three steps (tile_kernel.hpp),
+// which are
 // compiled apart from the rest of the library (tile.hip, one object per
 // precision form).
 #pragma once
@@ -7,6 +8,12 @@
 #include "lbm_ltne.h"
 
 namespace ltne {
+
+// Tiles of one lattice of a batch: shape, tiles along x, first entry of the
+// lattice in the batch's tile list.
+struct LatticeTiles {
+  int w, h, ntx, begin;
+};
 
 // Buffers of one lattice as byte offsets into the batch's single allocation,
 // whose base the kernels take as an argument: addresses formed from a kernel
@@ -22,9 +29,8 @@ struct CavityDesc {
   int tile_begin;    // first entry of this lattice in the combined tile list
   int wave_begin;    // first entry of this lattice in the two-step wavefront list
   int rows2;         // chunk height of its two-step wavefronts
-  int tile2_begin;   // first entry of this lattice in the two-step tile list
-  int tile2_w, tile2_h, tile2_ntx;  // its two-step tiles
   int pad_;
+  LatticeTiles tiles[2];  // of the launches of two and three steps
 };
 
 template <typename T>
@@ -32,11 +38,14 @@ __device__ __forceinline__ T* at_offset(char* base, long long off) {
   return off < 0 ? nullptr : reinterpret_cast<T*>(base + off);
 }
 
-// Tiles of a two-step launch over one lattice.
+// Most steps of a launch.
+constexpr int kTileSteps = 3;
+
+// Tiles of a launch over one lattice.
 struct TileGrid {
-  int w, h;     // output nodes of a tile, (w + 2) (h + 2) at most the kernel's slots
+  int w, h;     // output nodes of a tile; with its halo at most the kernel's slots
   int ntx;      // tiles along x
-  int ntiles;   // tiles of the lattice (0: the lattice does not take two-step tiles)
+  int ntiles;   // tiles of the lattice (0: the lattice takes no tiles)
   int per_xcd;  // tiles per XCD; the grid has 8 per_xcd workgroups
 };
 
@@ -44,13 +53,15 @@ struct TileGrid {
 // workgroups share a CU's 160 KB (19 populations a slot, 81472 bytes a
 // workgroup) and its wavefront slots -- 4 wavefronts per SIMD in the forms
 // whose node update needs 80 to 128 registers, 8 with binary16 storage (64).
-inline int tile2_slots(int precision) { return precision == LBM_FP64 ? 536 : (precision == LBM_FP16S ? 2144 : 1072); }
-inline int tile2_block(int precision) { return precision == LBM_FP16S ? 1024 : 512; }
+inline int tile_slots(int precision) { return precision == LBM_FP64 ? 536 : (precision == LBM_FP16S ? 2144 : 1072); }
 
-// The tile shape of one lattice's two-step launches.
-TileGrid tile2_grid(const lbm_ltne_params& p);
+// The tile shape of one lattice's launches of nsub (2 or 3) steps.
+TileGrid tile_grid(const lbm_ltne_params& p, int nsub);
 // Tile shapes of a batch's lattices (all of them, or none: ntiles = 0).
-void tile2_batch_grids(int n, const lbm_ltne_params* ps, TileGrid* out);
+void tile_batch_grids(int n, const lbm_ltne_params* ps, int nsub, TileGrid* out);
+// Steps of the next launch when left steps remain: three, and two where that
+// leaves no single step over.
+inline int next_steps(long long left) { return left == 1 ? 1 : (left == 2 || left == 4 ? 2 : 3); }
 
 struct TileLaunch {
   const void* consts;  // StepConsts of the lattice (host)
@@ -58,12 +69,13 @@ struct TileLaunch {
   void* dst;
   const void* phi;
   const void* hv;
-  void* mac;  // macros of the second step, or nullptr
+  void* mac;  // macros of the last step, or nullptr
   TileGrid grid;
-  uint32_t step;  // number of the first of the two steps
+  int nsub;       // steps
+  uint32_t step;  // number of the first of them
   hipStream_t stream;
 };
-hipError_t launch_tile2(int precision, const TileLaunch& a);
+hipError_t launch_tiles(int precision, const TileLaunch& a);
 
 struct BatchTileLaunch {
   char* base;
@@ -72,19 +84,20 @@ struct BatchTileLaunch {
   const int* tile_cav;  // lattice of every tile (device)
   int ntiles, fields, parity;
   bool macros;
+  int nsub;
   uint32_t step;
   hipStream_t stream;
 };
-hipError_t launch_batch_tile2(int precision, const BatchTileLaunch& a);
+hipError_t launch_batch_tiles(int precision, const BatchTileLaunch& a);
 
 // One object of tile.hip per form.
-hipError_t launch_tile2_f64(const TileLaunch& a);
-hipError_t launch_tile2_f32(const TileLaunch& a);
-hipError_t launch_tile2_f16s(const TileLaunch& a);
-hipError_t launch_tile2_f32sr(const TileLaunch& a);
-hipError_t launch_batch_tile2_f64(const BatchTileLaunch& a);
-hipError_t launch_batch_tile2_f32(const BatchTileLaunch& a);
-hipError_t launch_batch_tile2_f16s(const BatchTileLaunch& a);
-hipError_t launch_batch_tile2_f32sr(const BatchTileLaunch& a);
+hipError_t launch_tiles_f64(const TileLaunch& a);
+hipError_t launch_tiles_f32(const TileLaunch& a);
+hipError_t launch_tiles_f16s(const TileLaunch& a);
+hipError_t launch_tiles_f32sr(const TileLaunch& a);
+hipError_t launch_batch_tiles_f64(const BatchTileLaunch& a);
+hipError_t launch_batch_tiles_f32(const BatchTileLaunch& a);
+hipError_t launch_batch_tiles_f16s(const BatchTileLaunch& a);
+hipError_t launch_batch_tiles_f32sr(const BatchTileLaunch& a);
 
 }  // namespace ltne

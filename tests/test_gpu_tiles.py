@@ -1,4 +1,4 @@
-"""Two steps per launch over tiles: every precision form, at the edges of the
+"""Two and three steps per launch over tiles: every precision form, at the edges of the
 tiles (a last tile of one or two nodes, a single tile, the smallest lattices,
 periodic wraps inside one tile), bit for bit against single steps; and a batch
 of such lattices against the lattices alone."""
@@ -44,18 +44,15 @@ def _same(a, b):
 def test_tiles_equal_single_steps(B, form, size):
     p, phi, hv, tf, ts = _case(*size, FORMS[form])
     for fields in (dict(phi=phi, Hv=hv, Tf0=tf, Ts0=ts), dict(Tf0=tf, Ts0=ts), dict(phi=phi), dict(Hv=hv)):
-        one, two = B.Lattice(p, **fields), B.Lattice(p, **fields)
-        for _ in range(7):
-            one.step(1)
-        two.step(4)  # a call that ends with a pair
-        two.step(3)  # one that ends with a single step
-        _same(one.macros(), two.macros())
-        for _ in range(2):
-            one.step(1)
-        two.step(2)
-        _same(one.macros(), two.macros())
+        one, many = B.Lattice(p, **fields), B.Lattice(p, **fields)
+        for calls in ((4, 3), (8,), (2,)):  # 2 + 2, 3; 3 + 3 + 2; 2
+            for n in calls:
+                many.step(n)
+            for _ in range(sum(calls)):
+                one.step(1)
+            _same(one.macros(), many.macros())
         one.close()
-        two.close()
+        many.close()
 
 
 @pytest.mark.parametrize("form", FORMS)
