@@ -234,17 +234,19 @@ int lbm_ltne_load(lbm_ltne_t h, const void *host_buf, size_t bytes);
  * node (host arrays of nx*ny doubles, row-major; either may be NULL).  The
  * gradient is that of the discrete map actually computed: every step,
  * the wall reconstruction and, when the handle is still at t = 0, the
- * initialisation.  Checkpoints of the state are kept every ckpt_every steps
- * (< 1: one segment) and each segment is recomputed once while its
- * per-node sums are recorded, on a second stream of the library's own that
- * runs the recompute of one segment while the handle's stream sweeps the
- * next one back.  Work memory of about (nsteps/ckpt_every + 2) state copies
- * + 40 x ckpt_every bytes per node (binary32; two recording buffers, or one
- * with 20 x ckpt_every bytes per node when two do not fit, and then the
- * recompute and the sweep alternate) is allocated for the call.  FP64, FP32 and FP32SR forms
- * (LBM_EUNSUPPORTED for FP16 storage, and for a lattice with the correlation
- * of Eq. 52; the correction term of Sec. 3.2 is covered).  Synchronizes.  On an error the
- * lattice is left at its state on entry (unless the device itself failed).
+ * initialisation.  The steps are taken in segments of ckpt_every (< 1: one
+ * segment).  The last two are recorded while the lattice advances (the
+ * per-node sums of every step); of each earlier one the state at its start
+ * is kept and it is recomputed once, recording, on a second stream of the
+ * library's own while the handle's stream sweeps a later one back.  Work
+ * memory of about nsteps/ckpt_every state copies + 40 x ckpt_every bytes per
+ * node (binary32; two recording buffers, or one with 20 x ckpt_every bytes
+ * per node when two do not fit, and then only the last segment is recorded
+ * on the way and recompute and sweep alternate) is allocated for the call.
+ * FP64, FP32 and FP32SR forms (LBM_EUNSUPPORTED for FP16 storage, and for a
+ * lattice with the correlation of Eq. 52; the correction term of Sec. 3.2 is
+ * covered).  Synchronizes.  On an error the lattice is left at its state on
+ * entry (unless the device itself failed).
  */
 int lbm_ltne_adjoint(lbm_ltne_t h, int64_t nsteps, int64_t ckpt_every, double *loss, double *dL_dphi,
                      double *dL_dHv);

@@ -17,9 +17,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm_ltne.so")
 # Objects of the library: source, flags of its own.  tile.hip is compiled once
-# per precision form (see there for its flag).
+# per precision form (see there for the flag).
 TILE_FLAGS = ["-mllvm", "-disable-machine-licm"]
-OBJECTS = [("lbm_ltne.hip", []), ("params.hip", []), ("batch.hip", []), ("tile_shapes.hip", [])]
+OBJECTS = [("lbm_ltne.hip", []), ("params.hip", []), ("batch.hip", []), ("tile_shapes.hip", []),
+           ("adjoint_tile.hip", TILE_FLAGS)]
 OBJECTS += [("tile.hip", TILE_FLAGS + ["-DLTNE_TILE_FORM=%d" % form]) for form in range(4)]
 
 HIPCC_FLAGS = [

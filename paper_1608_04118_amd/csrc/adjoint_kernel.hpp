@@ -378,11 +378,22 @@ __device__ __forceinline__ bool wall_dirichlet(const StepConsts<C>& k, int x, in
 // Index one step outside [0, n) brought back by the periodic wrap.
 __device__ __forceinline__ int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
+// Where a sweep takes lambda from: mu_i of the previous sweep at (sx, sy), one
+// velocity away from (x, y), kept in device memory, one plane of P elements per
+// population.
+template <typename Lm>
+struct GlobalMu {
+  const Lm* __restrict__ mu;
+  long long P;
+  __device__ __forceinline__ Lm operator()(int i, int, int, int sx, int sy, int nx) const {
+    return mu[i * P + (sy * nx + sx)];
+  }
+};
+
 // lambda_i at node (x, y): mu_i of the previous sweep at (x, y) + e_i, or 0
-// when that node is a wall node or outside the lattice.
-template <typename Lm, typename C>
-__device__ __forceinline__ void gather_lambda(const Lm* __restrict__ mu, int x, int y, const StepConsts<C>& k,
-                                              const long long P, Lm (&lam)[19]) {
+// when that node is a wall node or outside the lattice.  Bulk: no neighbour is.
+template <bool Bulk, typename Lm, typename C, class Mu>
+__device__ __forceinline__ void gather_lambda(const Mu& mu, int x, int y, const StepConsts<C>& k, Lm (&lam)[19]) {
   const int nx = k.nx, ny = k.ny;
 #pragma unroll
   for (int i = 0; i < kPlanes; ++i) {
@@ -392,7 +403,7 @@ __device__ __forceinline__ void gather_lambda(const Lm* __restrict__ mu, int x, 
     if (k.py) sy = wrap1(sy, ny);
     const bool inside = sx >= 0 && sx < nx && sy >= 0 && sy < ny;
     const bool wall = (!k.px && (sx == 0 || sx == nx - 1)) || (!k.py && (sy == 0 || sy == ny - 1));
-    lam[i] = (inside && !wall) ? mu[i * P + (sy * nx + sx)] : Lm(0);
+    lam[i] = (Bulk || (inside && !wall)) ? mu(i, x, y, sx, sy, nx) : Lm(0);
   }
 }
 
@@ -481,56 +492,36 @@ __device__ __forceinline__ void quad_sum(MacroAdj<C>& b, RelaxAdj<Lm>& r) {
   }
 }
 
-// Lm: storage type of the adjoint populations, C: arithmetic type, R: type
-// of the lattice's fields and recorded sums.
 static_assert(kRows == 1, "the adjoint kernel takes one node (or one part of one) per lane");
 
-template <typename Lm, typename C, typename R, int Mode>
-__global__ __launch_bounds__(kBlock) void adjoint_kernel(
-    const Lm* __restrict__ lam_in, Lm* __restrict__ lam_out, const R* __restrict__ rec,
-    const R* __restrict__ phi_field, const R* __restrict__ hv_field, double* __restrict__ gphi,
-    double* __restrict__ ghv, const R* __restrict__ wseed, const R* __restrict__ init_tf,
-    const R* __restrict__ init_ts, const StepConsts<C> k, const AdjGrid g) {
-  const int b = blockIdx.x;
+// One node's part of a sweep.  Lm: storage type of the adjoint populations,
+// C: arithmetic type, R: type of the lattice's fields and recorded sums.
+// Bulk: a node not next to a wall, in a lane of its own; slot: the part of the
+// node that this lane takes otherwise (see AdjGrid);
+// mu_in(i, x, y, sx, sy, nx): the previous sweep's mu_i at (sx, sy), the node
+// one velocity away from (x, y); wall_grad(ib, gp, gh): adds to the gradients
+// of a wall node; done(iz, mu, gp, gh, m, D0): the results of
+// node iz, called by its lane of slot 0.
+template <typename Lm, typename C, typename R, int Mode, bool Bulk, class Mu, class WallGrad, class Done>
+__device__ __forceinline__ void adjoint_node(const int x, const int y, const int slot, const bool valid,
+                                             const Mu& mu_in, const R* __restrict__ rec,
+                                             const R* __restrict__ phi_field, const R* __restrict__ hv_field,
+                                             const R* __restrict__ wseed, const R* __restrict__ init_tf,
+                                             const R* __restrict__ init_ts, const StepConsts<C>& k,
+                                             const WallGrad& wall_grad, const Done& done) {
   const int nx = k.nx, ny = k.ny;
-  const long long P = g.lplane;
-  // ---- which node, and which part of it, this lane takes ----
-  int x, y, slot = 0;
-  bool valid;
-  if (b < g.bulk_blocks) {
-    const int t = (b & (kXcds - 1)) * g.tm.per_xcd + (b >> 3);
-    if (t >= g.tm.ntiles) return;
-    const int tw = 1 << g.tm.tw_shift;
-    const int xl = (t % g.tm.ntx) * tw + (static_cast<int>(threadIdx.x) & (tw - 1));
-    const int yl = (t / g.tm.ntx) * (kBlock >> g.tm.tw_shift) + (static_cast<int>(threadIdx.x) >> g.tm.tw_shift);
-    if (xl >= g.bw || yl >= g.bh) return;
-    x = g.bx0 + xl;
-    y = g.by0 + yl;
-    valid = true;
-  } else {
-    // four lanes per edge node; every lane of the wavefront stays to the
-    // cross-lane sums
-    const int e4 = (b - g.bulk_blocks) * kBlock + static_cast<int>(threadIdx.x);
-    const int e = e4 >> 2;
-    slot = e4 & 3;
-    valid = e < g.nedge;
-    x = 1;
-    y = 1;
-    if (valid) edge_node(e, g, nx, ny, x, y);
-  }
-  const bool edge = b >= g.bulk_blocks;
   const int iz = y * nx + x;
   // the wall this lane takes (slots 1-3), if any
   const int cx = (!k.px && x == 1) ? 0 : ((!k.px && x == nx - 2) ? nx - 1 : -1);
   const int cy = (!k.py && y == 1) ? 0 : ((!k.py && y == ny - 2) ? ny - 1 : -1);
-  const bool has_wall = edge && Mode != kAdjSeed &&
+  const bool has_wall = !Bulk && Mode != kAdjSeed &&
                         ((slot == 1 && cx >= 0) || (slot == 2 && cy >= 0) || (slot == 3 && cx >= 0 && cy >= 0));
   const bool active = valid && (slot == 0 || has_wall);
   const int ax = (slot == 2) ? x : cx, ay = (slot == 1) ? y : cy;  // wall node of slots 1-3
   // own (slot 0) or wall adjoint populations first, so the loads overlap the
   // arithmetic
   Lm lam[19];
-  if (Mode != kAdjSeed && active) gather_lambda(lam_in, slot == 0 ? x : ax, slot == 0 ? y : ay, k, P, lam);
+  if (Mode != kAdjSeed && active) gather_lambda<Bulk>(mu_in, slot == 0 ? x : ax, slot == 0 ? y : ay, k, lam);
   NodeMacros<C> m;
   C D0 = C(0);
   MacroAdj<C> bar;
@@ -563,7 +554,7 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(
     } else if (active) {
       MomAdj<Lm> L;
       mom_adjoint(lam, L);
-      if (slot == 0) {
+      if (Bulk || slot == 0) {
         adj_interior(m, L, bar, k);
       } else {
         const int ib = ay * nx + ax;
@@ -573,13 +564,12 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(
         const bool dir_w = wall_dirichlet(k, ax, ay, thw);
         C gpb = C(0), ghb = C(0);
         adj_wall(m, L, phb, hvb, dir_w, thw, bar, gpb, ghb, k);
-        gphi[ib] += static_cast<double>(gpb);
-        ghv[ib] += static_cast<double>(ghb);
+        wall_grad(ib, static_cast<double>(gpb), static_cast<double>(ghb));
       }
       relax_add(rx, L, k);
     }
   }
-  if (edge) quad_sum(bar, rx);
+  if (!Bulk) quad_sum(bar, rx);
   if (!valid || slot != 0) return;
   C nu[5], gpz, ghz;
   adj_backprop(m, bar, nu, gpz, ghz, k);
@@ -627,22 +617,60 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(
       o[4] = -w2 + w3 - w4 + ns;
     }
   }
-  double gpd = static_cast<double>(gpz), ghd = static_cast<double>(ghz);
-  if (Mode == kAdjInit) {
-    // the initial populations depend on phi, H through Sr(T_init):
-    // d g_f / dp = -w~ D0 d(d0)/dp, d h / dp = w~ D0 d(d0 + d1)/dp
-    const C w0 = C(1) - k.varpi, w1 = C(0.25) * k.varpi;
-    const C sa = w0 * C(mu[9]) + w1 * ((C(mu[10]) + C(mu[11])) + (C(mu[12]) + C(mu[13])));
-    const C sh = w0 * C(mu[14]) + w1 * ((C(mu[15]) + C(mu[16])) + (C(mu[17]) + C(mu[18])));
-    const C dd0_dphi = -m.d0 * m.ip, dd1_dphi = m.d1 * m.iq;
-    const C dd0_dh = C(0.5) * k.hvf * m.ip, dd1_dh = C(0.5) * k.hvf * k.inv_sigma * m.iq;
-    gpd += static_cast<double>((-sa * dd0_dphi + sh * (dd0_dphi + dd1_dphi)) * D0);
-    ghd += static_cast<double>((-sa * dd0_dh + sh * (dd0_dh + dd1_dh)) * D0);
+  done(iz, mu, static_cast<double>(gpz), static_cast<double>(ghz), m, D0);
+}
+
+template <typename Lm, typename C, typename R, int Mode>
+__global__ __launch_bounds__(kBlock) void adjoint_kernel(
+    const Lm* __restrict__ lam_in, Lm* __restrict__ lam_out, const R* __restrict__ rec,
+    const R* __restrict__ phi_field, const R* __restrict__ hv_field, double* __restrict__ gphi,
+    double* __restrict__ ghv, const R* __restrict__ wseed, const R* __restrict__ init_tf,
+    const R* __restrict__ init_ts, const StepConsts<C> k, const AdjGrid g) {
+  const int b = blockIdx.x;
+  const int nx = k.nx, ny = k.ny;
+  const long long P = g.lplane;
+  const GlobalMu<Lm> mu_in{lam_in, P};
+  auto wall_grad = [&](int ib, double gp, double gh) {
+    gphi[ib] += gp;
+    ghv[ib] += gh;
+  };
+  auto done = [&](int iz, const Lm (&mu)[19], double gpd, double ghd, const NodeMacros<C>& m, C D0) {
+    if (Mode == kAdjInit) {
+      // the initial populations depend on phi, H through Sr(T_init):
+      // d g_f / dp = -w~ D0 d(d0)/dp, d h / dp = w~ D0 d(d0 + d1)/dp
+      const C w0 = C(1) - k.varpi, w1 = C(0.25) * k.varpi;
+      const C sa = w0 * C(mu[9]) + w1 * ((C(mu[10]) + C(mu[11])) + (C(mu[12]) + C(mu[13])));
+      const C sh = w0 * C(mu[14]) + w1 * ((C(mu[15]) + C(mu[16])) + (C(mu[17]) + C(mu[18])));
+      const C dd0_dphi = -m.d0 * m.ip, dd1_dphi = m.d1 * m.iq;
+      const C dd0_dh = C(0.5) * k.hvf * m.ip, dd1_dh = C(0.5) * k.hvf * k.inv_sigma * m.iq;
+      gpd += static_cast<double>((-sa * dd0_dphi + sh * (dd0_dphi + dd1_dphi)) * D0);
+      ghd += static_cast<double>((-sa * dd0_dh + sh * (dd0_dh + dd1_dh)) * D0);
+    } else {
+      for (int i = 0; i < kPlanes; ++i) lam_out[i * P + iz] = mu[i];
+    }
+    gphi[iz] += gpd;
+    ghv[iz] += ghd;
+  };
+  if (b < g.bulk_blocks) {
+    const int t = (b & (kXcds - 1)) * g.tm.per_xcd + (b >> 3);
+    if (t >= g.tm.ntiles) return;
+    const int tw = 1 << g.tm.tw_shift;
+    const int xl = (t % g.tm.ntx) * tw + (static_cast<int>(threadIdx.x) & (tw - 1));
+    const int yl = (t / g.tm.ntx) * (kBlock >> g.tm.tw_shift) + (static_cast<int>(threadIdx.x) >> g.tm.tw_shift);
+    if (xl >= g.bw || yl >= g.bh) return;
+    adjoint_node<Lm, C, R, Mode, true>(g.bx0 + xl, g.by0 + yl, 0, true, mu_in, rec, phi_field, hv_field, wseed, init_tf,
+                                       init_ts, k, wall_grad, done);
   } else {
-    for (int i = 0; i < kPlanes; ++i) lam_out[i * P + iz] = mu[i];
+    // four lanes per edge node; every lane of the wavefront stays to the
+    // cross-lane sums
+    const int e4 = (b - g.bulk_blocks) * kBlock + static_cast<int>(threadIdx.x);
+    const int e = e4 >> 2;
+    const bool valid = e < g.nedge;
+    int x = 1, y = 1;
+    if (valid) edge_node(e, g, nx, ny, x, y);
+    adjoint_node<Lm, C, R, Mode, false>(x, y, e4 & 3, valid, mu_in, rec, phi_field, hv_field, wseed, init_tf, init_ts,
+                                        k, wall_grad, done);
   }
-  gphi[iz] += gpd;
-  ghv[iz] += ghd;
 }
 
 }  // namespace ltne

@@ -81,7 +81,7 @@ constexpr int kMacros = 4;    // write rho, u, T_f, T_s of this step
 constexpr int kInit = 8;      // build the t = 0 populations instead of streaming
 constexpr int kMacrosIf = 32;  // the same where the macro pointer is not null (uniform over the launch)
 constexpr int kInterior = 64;  // the node is no wall node (no wall code is compiled)
-constexpr int kRecord = 16;   // write q = (rho - rho0, j_x, j_y, sum g_f, sum h) at interior nodes
+constexpr int kRecord = 16;   // write q = (rho - rho0, j_x, j_y, sum g_f, sum h) at interior nodes (where the pointer is not null)
 
 // Mapping of workgroups to lattice tiles.  A tile is tw x (kRows 256 / tw)
 // nodes, tiles are numbered row-major, and workgroup b runs tile

@@ -139,8 +139,10 @@ hipError_t launch_step(const lbm_ltne* h, int mode, int64_t step, const void* sr
 
 
 // nsub (2 or 3) steps in one launch; with mac, the last one also writes the
-// macros (the last steps of a call).
-hipError_t launch_steps(const lbm_ltne* h, int nsub, int64_t step, const void* src, void* dst, void* mac) {
+// macros (the last steps of a call); with rec, every step records q at the
+// interior nodes (5 planes a step).
+hipError_t launch_steps(const lbm_ltne* h, int nsub, int64_t step, const void* src, void* dst, void* mac,
+                        void* rec = nullptr, hipStream_t stream = nullptr) {
   TileLaunch a{};
   a.consts = compute_bytes(h->p.precision) == 8 ? static_cast<const void*>(&h->kd) : static_cast<const void*>(&h->kf);
   a.src = src;
@@ -148,11 +150,26 @@ hipError_t launch_steps(const lbm_ltne* h, int nsub, int64_t step, const void* s
   a.phi = h->phi();
   a.hv = h->hv();
   a.mac = mac;
+  a.rec = rec;
   a.grid = h->tiles[nsub - 2];
   a.nsub = nsub;
   a.step = static_cast<uint32_t>(step);
-  a.stream = h->stream;
+  a.stream = stream ? stream : h->stream;
   return launch_tiles(h->p.precision, a);
+}
+
+// Whether the lattice takes launches of several steps.
+bool has_tiles(const lbm_ltne* h) { return h->tiles[0].ntiles > 0 && h->tiles[1].ntiles > 0; }
+
+// The next of `left` >= 1 steps (the first numbered step) in one launch, from
+// src to dst; returns their number in *nsub.  mac: macros of the last of them,
+// or nullptr; rec: recorded sums, or nullptr.
+hipError_t launch_some(const lbm_ltne* h, int64_t left, int64_t step, const void* src, void* dst, void* mac, void* rec,
+                       hipStream_t stream, int* nsub) {
+  *nsub = has_tiles(h) ? next_steps(left) : 1;
+  void* const m = *nsub == left ? mac : nullptr;
+  if (*nsub > 1) return launch_steps(h, *nsub, step, src, dst, m, rec, stream);
+  return launch_step(h, rec ? (m ? 4 : 3) : (m ? 1 : 0), step, src, dst, m, nullptr, nullptr, rec, stream);
 }
 
 // Copies a host double field to device memory in the compute type.
@@ -352,9 +369,7 @@ int lbm_ltne_step(lbm_ltne_t h, int64_t nsteps) {
   if (!h) return set_error(LBM_EINVAL, "handle is NULL");
   if (nsteps < 0) return set_error(LBM_EINVAL, "nsteps = %lld < 0", static_cast<long long>(nsteps));
   if (nsteps == 0) return LBM_OK;
-  const bool tiles = h->tiles[0].ntiles > 0 && h->tiles[1].ntiles > 0;
   const int64_t de = h->p.diag_every;
-  auto checked = [de](int64_t t) { return de > 0 && t % de == 0; };
   void* scratch_mac = h->mac(1 - h->mcur);  // overwritten by the call's last step
   int64_t s = 0;
   while (s < nsteps) {
@@ -362,24 +377,19 @@ int lbm_ltne_step(lbm_ltne_t h, int64_t nsteps) {
     // several steps in one launch up to the next checked step, which runs
     // alone; the launch that ends the call also writes the macros
     int64_t run = nsteps - s;
-    if (de > 0) run = std::min(run, de - 1 - h->steps % de);
-    if (tiles && run >= 2) {
-      const int nsub = next_steps(run);
-      const bool ends = s + nsub == nsteps;
-      hipError_t e = launch_steps(h, nsub, t, h->pop(h->cur), h->pop(1 - h->cur), ends ? scratch_mac : nullptr);
-      if (e != hipSuccess) return set_error(LBM_EHIP, "step launch: %s", hipGetErrorString(e));
-      h->cur = 1 - h->cur;
-      h->steps += nsub;
-      s += nsub;
-      continue;
-    }
-    const bool last = (s == nsteps - 1), check = checked(t);
-    hipError_t e = launch_step(h, (last || check) ? 1 : 0, t, h->pop(h->cur), h->pop(1 - h->cur),
-                               (last || check) ? scratch_mac : nullptr, nullptr, nullptr);
+    const bool check = de > 0 && t % de == 0;
+    if (check)
+      run = 1;
+    else if (de > 0)
+      run = std::min(run, de - t % de);
+    const bool ends = s + run == nsteps;
+    int nsub = 1;
+    hipError_t e = launch_some(h, run, t, h->pop(h->cur), h->pop(1 - h->cur), ends || check ? scratch_mac : nullptr,
+                               nullptr, nullptr, &nsub);
     if (e != hipSuccess) return set_error(LBM_EHIP, "step launch: %s", hipGetErrorString(e));
     h->cur = 1 - h->cur;
-    h->steps += 1;
-    s += 1;
+    h->steps += nsub;
+    s += nsub;
     if (check) {
       // binary64 mass and energy of this step's macros; a non-finite sum
       // records the step on the device (read by the next synchronizing call)
@@ -644,7 +654,11 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
   const size_t lamb = align_up(static_cast<size_t>(kPlanes) * ag.lplane * sizeof(Lm), kAlign);
   const size_t gb = align_up(n * sizeof(double), kAlign);
   const size_t fb = align_up(n * sizeof(R), kAlign);
-  auto total_for = [&](int nbuf) { return nseg * popb + 2 * popb + nbuf * recb + 2 * lamb + 2 * gb + 3 * fb; };
+  // checkpoints: those of the recomputed segments, and the first in any case
+  auto checkpoints = [&](int nbuf) { return std::max<int64_t>(1, nseg - nbuf); };
+  auto total_for = [&](int nbuf) {
+    return (checkpoints(nbuf) + 2) * popb + nbuf * recb + 2 * lamb + 2 * gb + 3 * fb;
+  };
 
   // Work memory, a second stream and its events, released on every path out
   // (after both streams drained).
@@ -662,12 +676,12 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
     }
   } wk;
   wk.main = h->stream;
-  // Segments are recomputed on the second stream into one of two recording
-  // buffers while the main stream sweeps the segment after them backwards
-  // from the other, so the two latency-bound kernels share the machine; with
-  // memory for one buffer only, recompute and sweep alternate.
-  int nbuf = 2;
-  if (hipMalloc(&wk.buf, total_for(2)) != hipSuccess) {
+  // The forward records the last segments into the recording buffers, two of
+  // them; each earlier segment is recomputed on the second stream into one
+  // while the main stream sweeps the segment after it backwards from the
+  // other; with memory for one buffer only, recompute and sweep alternate.
+  int nbuf = nseg > 1 ? 2 : 1;
+  if (hipMalloc(&wk.buf, total_for(nbuf)) != hipSuccess) {
     wk.buf = nullptr;
     (void)hipGetLastError();
     nbuf = 1;
@@ -695,7 +709,7 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
   hipEvent_t ev_sweep[2] = {wk.ev[3], wk.ev[4]};  // sweep done reading buffer i
 
   char* ckpt = wk.buf;
-  char* work[2] = {ckpt + nseg * popb, ckpt + nseg * popb + popb};
+  char* work[2] = {ckpt + checkpoints(nbuf) * popb, ckpt + (checkpoints(nbuf) + 1) * popb};
   R* rec[2] = {reinterpret_cast<R*>(work[1] + popb), reinterpret_cast<R*>(work[1] + popb + (nbuf - 1) * recb)};
   Lm* lam[2] = {reinterpret_cast<Lm*>(reinterpret_cast<char*>(rec[0]) + nbuf * recb),
                 reinterpret_cast<Lm*>(reinterpret_cast<char*>(rec[0]) + nbuf * recb + lamb)};
@@ -706,8 +720,11 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
   R* its = reinterpret_cast<R*>(reinterpret_cast<char*>(itf) + fb);
 
   // forward with checkpoints; the handle itself advances to t0 + nsteps.
-  // A failure after this point puts the state of t0 (checkpoint 0) back.
+  // The last nbuf segments are recorded on the way, into their buffers; the
+  // others only leave the checkpoint that they are recomputed from (segment
+  // 0's also puts the state of t0 back after a failure past this point).
   const int cur0 = h->cur;
+  const int64_t nrecompute = std::max<int64_t>(0, nseg - nbuf);
   auto bail = [&](int code) {
     (void)hipStreamSynchronize(wk.side);
     (void)hipStreamSynchronize(h->stream);
@@ -717,13 +734,20 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
     return code;
   };
   for (int64_t sg = 0; sg < nseg; ++sg) {
-    e = hipMemcpyAsync(ckpt + sg * popb, h->pop(h->cur), popb, hipMemcpyDeviceToDevice, h->stream);
-    if (e != hipSuccess) return sg == 0 ? hip_fail(e, "checkpoint") : bail(hip_fail(e, "checkpoint"));
+    if (sg == 0 || sg < nrecompute) {
+      e = hipMemcpyAsync(ckpt + sg * popb, h->pop(h->cur), popb, hipMemcpyDeviceToDevice, h->stream);
+      if (e != hipSuccess) return sg == 0 ? hip_fail(e, "checkpoint") : bail(hip_fail(e, "checkpoint"));
+    }
     const int64_t steps_in = std::min<int64_t>(K, nsteps - sg * K);
-    for (int64_t j = 0; j < steps_in; ++j) {
-      e = launch_step(h, 0, t0 + sg * K + j + 1, h->pop(h->cur), h->pop(1 - h->cur), nullptr, nullptr, nullptr);
+    R* const rb = sg >= nrecompute ? rec[sg % nbuf] : nullptr;
+    void* const mac = sg == nseg - 1 ? h->mac(1 - h->mcur) : nullptr;
+    for (int64_t j = 0; j < steps_in;) {
+      int nsub = 1;
+      e = launch_some(h, steps_in - j, t0 + sg * K + j + 1, h->pop(h->cur), h->pop(1 - h->cur), mac,
+                      rb ? rb + j * 5 * n : nullptr, nullptr, &nsub);
       if (e != hipSuccess) return bail(hip_fail(e, "forward launch"));
       h->cur = 1 - h->cur;
+      j += nsub;
     }
   }
   int rc = upload_compute<R>(h, nusselt_weights(h, w), wseed);
@@ -738,6 +762,24 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
                        ag);
     return hipGetLastError();
   };
+  // two sweeps in one launch
+  const TileGrid tiles2 = adjoint_tile_grid(h->p, sizeof(Lm) == 8 ? kAdjSlots64 : kAdjSlots32);
+  auto sweep2 = [&](const Lm* lin, Lm* lout, const R* rec1, const R* rec0) {
+    Adjoint2Launch a{};
+    a.consts = &k;
+    a.lam_in = lin;
+    a.lam_out = lout;
+    a.rec1 = rec1;
+    a.rec0 = rec0;
+    a.phi = phi_f;
+    a.hv = hv_f;
+    a.gphi = gphi;
+    a.ghv = ghv;
+    a.grid = tiles2;
+    a.lplane = ag.lplane;
+    a.stream = h->stream;
+    return launch_adjoint2<Lm, C, R>(a);
+  };
   int la = 0;
   // the recomputes read the checkpoints of the forward
   if ((e = hipEventRecord(ev_fwd, h->stream)) != hipSuccess) return bail(hip_fail(e, "event record"));
@@ -745,24 +787,26 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
   for (int64_t sg = nseg - 1; sg >= 0; --sg) {
     const int b = static_cast<int>(sg % nbuf);
     R* rb = rec[b];
-    // recompute the segment on the side stream, recording q of every step,
-    // once the sweep that last read this buffer (segment sg + nbuf) is done
-    if (sg + nbuf <= nseg - 1 && (e = hipStreamWaitEvent(wk.side, ev_sweep[b], 0)) != hipSuccess)
-      return bail(hip_fail(e, "event wait"));
-    e = hipMemcpyAsync(work[0], ckpt + sg * popb, popb, hipMemcpyDeviceToDevice, wk.side);
-    if (e != hipSuccess) return bail(hip_fail(e, "restore"));
     const int64_t steps_in = std::min<int64_t>(K, nsteps - sg * K);
-    int wc = 0;
-    for (int64_t j = 1; j <= steps_in; ++j) {
-      const bool last = (sg == nseg - 1 && j == steps_in);
-      e = launch_step(h, last ? 4 : 3, t0 + sg * K + j, work[wc], work[1 - wc],
-                      last ? h->mac(1 - h->mcur) : nullptr, nullptr, nullptr, rb + (j - 1) * 5 * n, wk.side);
-      if (e != hipSuccess) return bail(hip_fail(e, "recompute launch"));
-      wc = 1 - wc;
+    if (sg < nrecompute) {
+      // recompute the segment on the side stream, recording q of every step,
+      // once the sweep that last read this buffer (segment sg + nbuf) is done
+      if ((e = hipStreamWaitEvent(wk.side, ev_sweep[b], 0)) != hipSuccess) return bail(hip_fail(e, "event wait"));
+      e = hipMemcpyAsync(work[0], ckpt + sg * popb, popb, hipMemcpyDeviceToDevice, wk.side);
+      if (e != hipSuccess) return bail(hip_fail(e, "restore"));
+      int wc = 0;
+      for (int64_t j = 0; j < steps_in;) {
+        int nsub = 1;
+        e = launch_some(h, steps_in - j, t0 + sg * K + j + 1, work[wc], work[1 - wc], nullptr, rb + j * 5 * n,
+                        wk.side, &nsub);
+        if (e != hipSuccess) return bail(hip_fail(e, "recompute launch"));
+        wc = 1 - wc;
+        j += nsub;
+      }
+      if ((e = hipEventRecord(ev_rec[b], wk.side)) != hipSuccess) return bail(hip_fail(e, "event record"));
+      if ((e = hipStreamWaitEvent(h->stream, ev_rec[b], 0)) != hipSuccess) return bail(hip_fail(e, "event wait"));
     }
-    if ((e = hipEventRecord(ev_rec[b], wk.side)) != hipSuccess) return bail(hip_fail(e, "event record"));
     // sweep it backwards on the main stream
-    if ((e = hipStreamWaitEvent(h->stream, ev_rec[b], 0)) != hipSuccess) return bail(hip_fail(e, "event wait"));
     int64_t jhi = steps_in;
     if (sg == nseg - 1) {
       e = sweep(adjoint_kernel<Lm, C, R, kAdjSeed>, nullptr, lam[la], rb + (steps_in - 1) * 5 * n, wseed,
@@ -770,9 +814,15 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
       if (e != hipSuccess) return bail(hip_fail(e, "seed launch"));
       jhi = steps_in - 1;
     }
-    for (int64_t j = jhi; j >= 1; --j) {
-      e = sweep(adjoint_kernel<Lm, C, R, kAdjStep>, lam[la], lam[1 - la], rb + (j - 1) * 5 * n, nullptr, nullptr,
-                nullptr);
+    for (int64_t j = jhi; j >= 1;) {
+      const R* rj = rb + (j - 1) * 5 * n;
+      if (j >= 2 && tiles2.ntiles > 0) {
+        e = sweep2(lam[la], lam[1 - la], rj, rj - 5 * n);
+        j -= 2;
+      } else {
+        e = sweep(adjoint_kernel<Lm, C, R, kAdjStep>, lam[la], lam[1 - la], rj, nullptr, nullptr, nullptr);
+        j -= 1;
+      }
       if (e != hipSuccess) return bail(hip_fail(e, "adjoint launch"));
       la = 1 - la;
     }

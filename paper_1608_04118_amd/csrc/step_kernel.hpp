@@ -425,7 +425,7 @@ __device__ __forceinline__ void node_update_with(
   T ths = thf + D;
 
   if constexpr ((F & kRecord) != 0) {
-    if (!wall) {
+    if (!wall && rec != nullptr) {
       const int ir = y * nx + x;
       rec[0 * k.mplane + ir] = drho;
       rec[1 * k.mplane + ir] = jx;

@@ -33,10 +33,19 @@ void tiles_ft(const TileLaunch& a) {
   hipLaunchKernelGGL((tile_kernel<TS, TC, F, T>), dim3(kXcds * a.grid.per_xcd), dim3(TileForm<TS, TC>::Block), 0,
                      a.stream, *static_cast<const StepConsts<TC>*>(a.consts), static_cast<const TS*>(a.src),
                      static_cast<TS*>(a.dst), static_cast<const TC*>(a.phi), static_cast<const TC*>(a.hv),
-                     static_cast<TC*>(a.mac), a.grid, a.step);
+                     static_cast<TC*>(a.mac), static_cast<TC*>(a.rec), a.grid, a.step);
 }
 template <int F>
 void tiles_f(const TileLaunch& a) {
+  if constexpr (sizeof(TS) > 2) {  // (no adjoint in binary16 storage)
+    if (a.rec) {
+      if (a.nsub == 3)
+        tiles_ft<F | kRecord, 3>(a);
+      else
+        tiles_ft<F | kRecord, 2>(a);
+      return;
+    }
+  }
   if (a.nsub == 3)
     tiles_ft<F, 3>(a);
   else

@@ -267,13 +267,13 @@ __device__ __forceinline__ void for_rect(const TileRect& r, const int t, const i
   }
 }
 
-// T steps of a tile.
+// T steps of a tile.  rec (F & kRecord): 5 planes of recorded sums per step.
 template <typename S, typename C, int F, int N, int T>
 __device__ __forceinline__ void tile_body(const int tx, const int ty, const int w, const int h, const int t,
                                           const int nthreads, const S* __restrict__ src, S* __restrict__ dst,
                                           const C* __restrict__ phi_field, const C* __restrict__ hv_field,
-                                          C* __restrict__ mac, ConstK<C>* kp, S* __restrict__ pops,
-                                          const uint32_t step) {
+                                          C* __restrict__ mac, C* __restrict__ rec, ConstK<C>* kp,
+                                          S* __restrict__ pops, const uint32_t step) {
   using Th = thermal_t<S, C>;
   const StepConsts<C>& k = *(const StepConsts<C>*)kp;
   const int nx = k.nx, ny = k.ny;
@@ -281,6 +281,15 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
   const int P = x1 - x0 + 2 * (T - 1);
   const int y0 = tile_bound(ty, h, ny), y1 = tile_bound(ty + 1, h, ny);
   auto slot = [&](int x, int y) { return pops + (y - y0 + T - 1) * P + (x - x0 + T - 1); };
+  // where step s (0, 1, ...) records this node: a node of the tile, once
+  auto record = [&](int s, int x, int y) -> C* {
+    if constexpr ((F & kRecord) != 0) {
+      const bool own = x >= x0 && x < x1 && y >= y0 && y < y1;
+      return own ? rec + s * (5 * k.mplane) : nullptr;
+    } else {
+      return nullptr;
+    }
+  };
   auto wrap = [&](int& x, int& y) {
     if (k.px) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
     if (k.py) y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
@@ -293,8 +302,9 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
     for_rect(r, t, nthreads, [&](int x, int y) {
       const StepConsts<C>& kk = fresh<C>(kp);
       SinkPut<S, OppSink<S, N>> put{{slot(x, y)}};
+      C* const rc = record(0, x, y);
       wrap(x, y);
-      node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step, nullptr,
+      node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step, rc,
                                 thermal_k<Th>(kk));
     });
   }
@@ -318,19 +328,20 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
         wrap(x, y);
         const AaPull<S, C, N, true> pull{a, x, y, P};
         SinkPut<S, ScatterSink<S, N>> put{{a, P}};
-        node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step + 1u,
-                                  nullptr, thermal_k<Th>(kk));
+        node_update_with<S, C, F & ~kRecord>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk,
+                                             step + 1u, nullptr, thermal_k<Th>(kk));
       }
       __syncthreads();
     }
     for_rect({ax0, ax0 + aw, ay0, ay0 + ah}, t, nthreads, [&](int x, int y) {
       const StepConsts<C>& kk = fresh<C>(kp);
       S* a = slot(x, y);
+      C* const rc = record(1, x, y);
       wrap(x, y);
       const AaPull<S, C, N, true> pull{a, x, y, P};
       SinkPut<S, ScatterSink<S, N>> put{{a, P}};
       node_update_with<S, C, F | kInterior>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk,
-                                            step + 1u, nullptr, thermal_k<Th>(kk));
+                                            step + 1u, rc, thermal_k<Th>(kk));
     });
     __syncthreads();
   }
@@ -343,7 +354,8 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
       const AaPull<S, C, N, T == 2> pull{slot(x, y), x, y, P};
       SinkPut<S, BufSink<S>> put{{d, (y - y0) * R + x * E, Q}};
       node_update_with<S, C, F | kMacrosIf>(x, y, pull, put, phi_field, hv_field, mac, nullptr, nullptr, kk,
-                                            step + static_cast<uint32_t>(T - 1), nullptr, thermal_k<Th>(kk));
+                                            step + static_cast<uint32_t>(T - 1), record(T - 1, x, y),
+                                            thermal_k<Th>(kk));
     });
   }
 }
@@ -359,7 +371,8 @@ struct TileForm {
 template <typename S, typename C, int F, int T>
 __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) void tile_kernel(
     const StepConsts<C> k, const S* __restrict__ src, S* __restrict__ dst, const C* __restrict__ phi_field,
-    const C* __restrict__ hv_field, C* __restrict__ mac, const TileGrid m, const uint32_t step) {
+    const C* __restrict__ hv_field, C* __restrict__ mac, C* __restrict__ rec, const TileGrid m,
+    const uint32_t step) {
   using Form = TileForm<S, C>;
   (void)k;  // read through the kernel's argument segment, where it is the first argument
   __shared__ S pops[kPlanes * Form::N];
@@ -367,7 +380,7 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   const int tile = (b & (kXcds - 1)) * m.per_xcd + (b >> 3);
   if (tile >= m.ntiles) return;
   tile_body<S, C, F, Form::N, T>(tile % m.ntx, tile / m.ntx, m.w, m.h, static_cast<int>(threadIdx.x), Form::Block,
-                                 src, dst, phi_field, hv_field, mac,
+                                 src, dst, phi_field, hv_field, mac, rec,
                                  (ConstK<C>*)__builtin_amdgcn_kernarg_segment_ptr(), pops, step);
 }
 
@@ -390,7 +403,8 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   tile_body<S, C, F, Form::N, T>(local % g.ntx, local / g.ntx, g.w, g.h, static_cast<int>(threadIdx.x), Form::Block,
                                  at_offset<const S>(base, d.pop[parity]), at_offset<S>(base, d.pop[parity ^ 1]),
                                  at_offset<const C>(base, d.phi), at_offset<const C>(base, d.hv),
-                                 macros ? at_offset<C>(base, d.mac) : nullptr, (ConstK<C>*)ks + c, pops, step);
+                                 macros ? at_offset<C>(base, d.mac) : nullptr, nullptr, (ConstK<C>*)ks + c, pops,
+                                 step);
 }
 
 }  // namespace ltne

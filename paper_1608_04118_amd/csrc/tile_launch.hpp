@@ -70,6 +70,7 @@ struct TileLaunch {
   const void* phi;
   const void* hv;
   void* mac;  // macros of the last step, or nullptr
+  void* rec;  // recorded sums of every step (5 planes each), or nullptr (not in binary16 storage)
   TileGrid grid;
   int nsub;       // steps
   uint32_t step;  // number of the first of them
@@ -99,5 +100,28 @@ hipError_t launch_batch_tiles_f64(const BatchTileLaunch& a);
 hipError_t launch_batch_tiles_f32(const BatchTileLaunch& a);
 hipError_t launch_batch_tiles_f16s(const BatchTileLaunch& a);
 hipError_t launch_batch_tiles_f32sr(const BatchTileLaunch& a);
+
+// Two steps of the adjoint sweep in one launch.  Slots of a workgroup's tile
+// and halo: 19 populations and two gradients each in half a CU's LDS.
+constexpr int kAdjSlots64 = 480;
+constexpr int kAdjSlots32 = 880;
+struct Adjoint2Launch {
+  const void* consts;  // StepConsts in the sweep's arithmetic type (host)
+  const void* lam_in;
+  void* lam_out;
+  const void* rec1;  // recorded sums of the later step
+  const void* rec0;  // and of the one before it
+  const void* phi;
+  const void* hv;
+  double* gphi;
+  double* ghv;
+  TileGrid grid;
+  long long lplane;
+  hipStream_t stream;
+};
+template <typename Lm, typename C, typename R>
+hipError_t launch_adjoint2(const Adjoint2Launch& a);
+// The tile shape of a lattice's two-step sweeps (slots: one of the above).
+TileGrid adjoint_tile_grid(const lbm_ltne_params& p, int slots);
 
 }  // namespace ltne

@@ -97,6 +97,8 @@ TileGrid tile_grid(const lbm_ltne_params& p, int nsub) {
   return best_shape(p, nsub, tile_slots(p.precision), true);
 }
 
+TileGrid adjoint_tile_grid(const lbm_ltne_params& p, int slots) { return best_shape(p, 2, slots, true); }
+
 // A batch: each lattice takes the shape with the fewest passes in all; the
 // largest tile size allowed is the one whose estimate for the whole batch
 // (tiles per CU, rounded up, times the mean passes of a tile) is smallest, so

@@ -68,3 +68,22 @@ def test_batch_tiles_equal_single_lattices(B, form):
         _same(lat.macros(), batch.macros(i))
         lat.close()
     batch.close()
+
+
+@pytest.mark.parametrize("form", ["f64", "f32", "f32sr"])
+@pytest.mark.parametrize("size", [s for s in SIZES if not (s[2] and s[3])], ids=lambda s: "%dx%d_p%d%d" % s)
+def test_adjoint_tiles_equal_single_sweeps(B, form, size):
+    """Segments of one step take single recorded steps and single sweeps;
+    longer ones the launches of several steps and of two sweeps."""
+    p, phi, hv, tf, ts = _case(*size, FORMS[form])
+    for n, every in ((2, 0), (7, 0), (12, 4)):
+        out = []
+        for k in (1, every):
+            lat = B.Lattice(p, phi=phi, Hv=hv, Tf0=tf, Ts0=ts)
+            lat.step(1)
+            out.append(lat.adjoint(n, ckpt_every=k) + (lat.macros(),))
+            lat.close()
+        a, b = out
+        assert a[0] == b[0] and np.abs(a[1]).max() > 0
+        assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+        _same(a[3], b[3])
