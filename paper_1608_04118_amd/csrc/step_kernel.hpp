@@ -189,21 +189,45 @@ __device__ __forceinline__ T thermal_rcp(T v) {
   }
 }
 
-template <typename C>
-__device__ __forceinline__ C dev_rsqrt(C v) {
-  if constexpr (std::is_same<C, double>::value) {
-    return dev_rcp(sqrt(v));
-  } else {
-    return __builtin_amdgcn_rsqf(v);
-  }
+// Correctly rounded square root.  The compiler's expansion of sqrt scales its
+// argument for the ends of the range and selects the special values; where
+// neither is needed -- binary32 from 2^-102, binary64 from 2^-767 to the
+// largest number -- the reciprocal square root estimate and the residual
+// x - s^2 give the same bits in 5 (binary32) and 10 instructions instead of 16
+// and 17: s = x y, s + (x - s^2) y / 2 in binary32 (compared with the
+// correctly rounded root for every binary32 number), and one coupled Newton
+// step for (s, y / 2) and two residual steps in binary64.  Other arguments
+// (fluid at rest, overflow, NaN) take the compiler's.  Two square roots a node
+// and step: 4096^2 binary32 270.5 to 264.6 us a step, 3072 x 2048 binary16
+// 88.5 to 86.5, 4096 x 2048 binary64 229.7 to 228.2.
+__device__ __forceinline__ float sqrt_rn(float x) {
+  if (__builtin_bit_cast(unsigned, x) - 0x0c800000u >= 0x7f800000u - 0x0c800000u) return __builtin_sqrtf(x);
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float s = x * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+}
+__device__ __forceinline__ double sqrt_rn(double x) {
+  const unsigned hi = static_cast<unsigned>(__builtin_bit_cast(unsigned long long, x) >> 32);
+  if (hi - 0x10000000u >= 0x7ff00000u - 0x10000000u) return sqrt(x);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double s0 = x * y, h0 = 0.5 * y;
+  const double r = __builtin_fma(-h0, s0, 0.5);
+  const double s1 = __builtin_fma(s0, r, s0), h1 = __builtin_fma(h0, r, h0);
+  const double s2 = __builtin_fma(__builtin_fma(-s1, s1, x), h1, s1);
+  return __builtin_fma(__builtin_fma(-s2, s2, x), h1, s2);
 }
 
 template <typename C>
 __device__ __forceinline__ C dev_sqrt(C v) {
+  return sqrt_rn(v);
+}
+
+template <typename C>
+__device__ __forceinline__ C dev_rsqrt(C v) {
   if constexpr (std::is_same<C, double>::value) {
-    return sqrt(v);
+    return dev_rcp(sqrt_rn(v));
   } else {
-    return __builtin_sqrtf(v);
+    return __builtin_amdgcn_rsqf(v);
   }
 }
 
