@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "liblbm_ltne.so")
 # per precision form (see there for the flag).
 TILE_FLAGS = ["-mllvm", "-disable-machine-licm"]
 OBJECTS = [("lbm_ltne.hip", []), ("params.hip", []), ("batch.hip", []), ("tile_shapes.hip", []),
-           ("adjoint_tile.hip", TILE_FLAGS)]
+           ("readback.hip", []), ("adjoint_tile.hip", TILE_FLAGS)]
 OBJECTS += [("tile.hip", TILE_FLAGS + ["-DLTNE_TILE_FORM=%d" % form]) for form in range(4)]
 
 HIPCC_FLAGS = [

@@ -238,6 +238,8 @@ struct lbm_ltne_batch {
   int grid2 = 0;      // workgroups of the persistent two-step launch (FP32)
   size_t consts_bytes = 0, desc_bytes = 0;
   long long nodes = 0;
+  Staging staging;  // of lbm_ltne_batch_macros
+  bool barriers = false;  // a persistent launch was queued, so ctl may hold a timeout
 
   long long n_of(int i) const { return static_cast<long long>(p[i].nx) * p[i].ny; }
 };
@@ -389,6 +391,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
     int npairs = (nsteps - (macros_last ? 1 : 0)) / 2;
     int parity = b->parity;
     if (npairs > 0) {
+      b->barriers = true;
       HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(BatchCtl), b->stream));
       const void* waves = b->base + b->off_waves;
       int nw = b->nwaves2;
@@ -409,6 +412,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
     }
     b->parity = parity;
   } else if (b->persistent) {
+    b->barriers = true;
     HIP_TRY(hipMemsetAsync(ctl, 0, sizeof(BatchCtl), b->stream));
     int parity = b->parity;
     uint32_t step0 = static_cast<uint32_t>(b->steps + 1);
@@ -849,25 +853,12 @@ int lbm_ltne_batch_macros(lbm_ltne_batch_t b, int32_t i, double* rho, double* ux
                           double* Tf, double* Ts) {
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
   if (i < 0 || i >= b->n) return set_error(LBM_EINVAL, "lattice index %d out of range", i);
-  int rc = check_ctl(b);
+  int rc = b->barriers ? check_ctl(b) : LBM_OK;
   if (rc != LBM_OK) return rc;
   const long long n = b->n_of(i);
   const size_t cb = compute_bytes(b->precision);
-  double* outs[5] = {rho, ux, uy, Tf, Ts};
-  std::vector<float> tmp;
-  for (int f = 0; f < 5; ++f) {
-    if (!outs[f]) continue;
-    const char* src = b->base + b->off_mac[i] + static_cast<size_t>(f) * n * cb;
-    if (cb == 8) {
-      HIP_TRY(hipMemcpyAsync(outs[f], src, n * 8, hipMemcpyDeviceToHost, b->stream));
-      HIP_TRY(hipStreamSynchronize(b->stream));
-    } else {
-      tmp.resize(n);
-      HIP_TRY(hipMemcpyAsync(tmp.data(), src, n * 4, hipMemcpyDeviceToHost, b->stream));
-      HIP_TRY(hipStreamSynchronize(b->stream));
-      for (long long j = 0; j < n; ++j) outs[f][j] = tmp[j];
-    }
-  }
+  double* const outs[5] = {rho, ux, uy, Tf, Ts};
+  HIP_TRY(read_fields(b->staging, b->device, b->stream, b->base + b->off_mac[i], static_cast<int>(cb), n, outs));
   return LBM_OK;
 }
 

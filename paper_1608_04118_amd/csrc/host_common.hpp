@@ -8,6 +8,7 @@
 #include "common.hpp"
 #include "lbm_ltne.h"
 #include "params.hpp"
+#include "readback.hpp"
 #include "reduce_kernels.hpp"
 
 namespace ltne {

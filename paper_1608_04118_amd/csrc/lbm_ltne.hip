@@ -35,6 +35,7 @@ struct lbm_ltne {
   StepConsts<float> kf{};
   std::vector<double> tf0, ts0;  // initial temperature fields (if given), for the adjoint
   TileGrid tiles[2] = {};  // tiles of the launches of two and three steps
+  Staging staging;         // of lbm_ltne_macros
 
   void* pop(int i) const { return base + lay.off_pop[i]; }
   void* mac(int i) const { return base + lay.off_mac[i]; }
@@ -411,21 +412,8 @@ int lbm_ltne_macros(lbm_ltne_t h, double* rho, double* ux, double* uy, double* T
   if (!h) return set_error(LBM_EINVAL, "handle is NULL");
   const long long n = h->n();
   const size_t cb = compute_bytes(h->p.precision);
-  double* outs[5] = {rho, ux, uy, Tf, Ts};
-  std::vector<float> tmp;
-  for (int f = 0; f < 5; ++f) {
-    if (!outs[f]) continue;
-    const char* src = static_cast<const char*>(h->mac(h->mcur)) + static_cast<size_t>(f) * n * cb;
-    if (cb == 8) {
-      HIP_TRY(hipMemcpyAsync(outs[f], src, n * 8, hipMemcpyDeviceToHost, h->stream));
-      HIP_TRY(hipStreamSynchronize(h->stream));
-    } else {
-      tmp.resize(n);
-      HIP_TRY(hipMemcpyAsync(tmp.data(), src, n * 4, hipMemcpyDeviceToHost, h->stream));
-      HIP_TRY(hipStreamSynchronize(h->stream));
-      for (long long i = 0; i < n; ++i) outs[f][i] = tmp[i];
-    }
-  }
+  double* const outs[5] = {rho, ux, uy, Tf, Ts};
+  HIP_TRY(read_fields(h->staging, h->device, h->stream, h->mac(h->mcur), static_cast<int>(cb), n, outs));
   return check_diverged(h, LBM_OK);
 }
 
