@@ -118,7 +118,8 @@ __device__ __forceinline__ C unscale(S v, C inv_scale) {
 // wrapped (uniform over the workgroup): the tile's rows run across the
 // periodic y axis, so they are not within 32 bits of one another; then every
 // row has its 64-bit address.
-template <typename S, typename C>
+// Inner: no node of the tile or its halo lies next to the lattice's edge.
+template <typename S, typename C, bool Inner>
 struct TilePull {
   const S* src;
   __amdgpu_buffer_rsrc_t r;
@@ -127,13 +128,13 @@ struct TilePull {
   __device__ __forceinline__ void operator()(int xc, int yc, const StepConsts<C>& k, C (&v)[kPlanes]) const {
     const int nx = k.nx, ny = k.ny;
     int xm = xc - 1, xp = xc + 1;
-    if (k.px) {
+    if (!Inner && k.px) {
       xm = (xc == 0) ? nx - 1 : xm;
       xp = (xc == nx - 1) ? 0 : xp;
     }
     const C isf = k.inv_sf, isg = k.inv_sg;
     S g[kPlanes];
-    if (wrapped) {
+    if (!Inner && wrapped) {
       const int ym = (yc == 0) ? ny - 1 : yc - 1, yp = (yc == ny - 1) ? 0 : yc + 1;
       const S *s0 = src + yc * k.rs, *sm = src + ym * k.rs, *sp = src + yp * k.rs;
 #pragma unroll
@@ -267,6 +268,16 @@ __device__ __forceinline__ void for_rect(const TileRect& r, const int t, const i
   }
 }
 
+// Whether tile t and what its T steps read stay off the ends of the axis.  Such
+// a tile takes a body without wall code and without wraps, some 40 of the 490
+// vector instructions (binary32) of a node: 4096^2 binary32 268.3 to 252.0 us
+// a step, binary16 storage (3072 x 2048) 86.4 to 81.3, binary64 (4096 x 2048)
+// 231.8 to 226.3, 1500 x 1100 f32sr 38.4 to 37.2, 1024^2 binary32 17.8 to 17.4.
+template <int T>
+__device__ __forceinline__ bool tile_inside(int t, int w, int n) {
+  return t * w >= T && tile_bound(t + 1, w, n) + T <= n;
+}
+
 // T steps of a tile.  rec (F & kRecord): 5 planes of recorded sums per step.
 template <typename S, typename C, int F, int N, int T>
 __device__ __forceinline__ void tile_body(const int tx, const int ty, const int w, const int h, const int t,
@@ -290,15 +301,17 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
       return nullptr;
     }
   };
+  constexpr bool inner = (F & kInterior) != 0;
   auto wrap = [&](int& x, int& y) {
+    if (inner) return;
     if (k.px) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
     if (k.py) y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
   };
   {
     const TileRect r = grown(x0, x1, y0, y1, T - 1, k);
-    const bool wrapped = k.py && (r.y0 < 1 || r.y1 > ny - 1);
+    const bool wrapped = !inner && k.py && (r.y0 < 1 || r.y1 > ny - 1);
     const int yb = wrapped ? 0 : max(r.y0 - 1, 0);
-    const TilePull<S, C> pull{src, rows_rsrc(src, yb, ny, k.rs), yb, wrapped};
+    const TilePull<S, C, inner> pull{src, rows_rsrc(src, yb, ny, k.rs), yb, wrapped};
     for_rect(r, t, nthreads, [&](int x, int y) {
       const StepConsts<C>& kk = fresh<C>(kp);
       SinkPut<S, OppSink<S, N>> put{{slot(x, y)}};
@@ -318,7 +331,7 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
     const int nb = (!k.py && r.y0 == 0) ? r.x1 - r.x0 : 0, nt = (!k.py && r.y1 == ny) ? r.x1 - r.x0 : 0;
     const int nl = (!k.px && r.x0 == 0) ? ah : 0, nr = (!k.px && r.x1 == nx) ? ah : 0;
     const int nw = nb + nt + nl + nr;
-    if (nw > 0) {
+    if (!inner && nw > 0) {
       for (int n = t; n < nw; n += nthreads) {
         const StepConsts<C>& kk = fresh<C>(kp);
         const int c = n - nb - nt;
@@ -379,9 +392,16 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   const int b = blockIdx.x;
   const int tile = (b & (kXcds - 1)) * m.per_xcd + (b >> 3);
   if (tile >= m.ntiles) return;
-  tile_body<S, C, F, Form::N, T>(tile % m.ntx, tile / m.ntx, m.w, m.h, static_cast<int>(threadIdx.x), Form::Block,
-                                 src, dst, phi_field, hv_field, mac, rec,
-                                 (ConstK<C>*)__builtin_amdgcn_kernarg_segment_ptr(), pops, step);
+  const int tx = tile % m.ntx, ty = tile / m.ntx;
+  ConstK<C>* const kp = (ConstK<C>*)__builtin_amdgcn_kernarg_segment_ptr();
+  auto body = [&](auto f) {
+    tile_body<S, C, decltype(f)::value, Form::N, T>(tx, ty, m.w, m.h, static_cast<int>(threadIdx.x), Form::Block, src,
+                                                    dst, phi_field, hv_field, mac, rec, kp, pops, step);
+  };
+  if (tile_inside<T>(tx, m.w, kp->nx) && tile_inside<T>(ty, m.h, kp->ny))
+    body(std::integral_constant<int, F | kInterior>{});
+  else
+    body(std::integral_constant<int, F>{});
 }
 
 // The same over every lattice of a batch: tile t belongs to lattice tile_cav[t].
@@ -400,11 +420,18 @@ __global__ __launch_bounds__((TileForm<S, C>::Block), (TileForm<S, C>::Waves)) v
   const CavityDesc<C>& d = *(const CavityDesc<C>*)((ConstD*)cav + c);
   const LatticeTiles& g = d.tiles[T - 2];
   const int local = tile - g.begin;
-  tile_body<S, C, F, Form::N, T>(local % g.ntx, local / g.ntx, g.w, g.h, static_cast<int>(threadIdx.x), Form::Block,
-                                 at_offset<const S>(base, d.pop[parity]), at_offset<S>(base, d.pop[parity ^ 1]),
-                                 at_offset<const C>(base, d.phi), at_offset<const C>(base, d.hv),
-                                 macros ? at_offset<C>(base, d.mac) : nullptr, nullptr, (ConstK<C>*)ks + c, pops,
-                                 step);
+  const int tx = local % g.ntx, ty = local / g.ntx;
+  ConstK<C>* const kp = (ConstK<C>*)ks + c;
+  auto body = [&](auto f) {
+    tile_body<S, C, decltype(f)::value, Form::N, T>(
+        tx, ty, g.w, g.h, static_cast<int>(threadIdx.x), Form::Block, at_offset<const S>(base, d.pop[parity]),
+        at_offset<S>(base, d.pop[parity ^ 1]), at_offset<const C>(base, d.phi), at_offset<const C>(base, d.hv),
+        macros ? at_offset<C>(base, d.mac) : nullptr, nullptr, kp, pops, step);
+  };
+  if (tile_inside<T>(tx, g.w, kp->nx) && tile_inside<T>(ty, g.h, kp->ny))
+    body(std::integral_constant<int, F | kInterior>{});
+  else
+    body(std::integral_constant<int, F>{});
 }
 
 }  // namespace ltne
