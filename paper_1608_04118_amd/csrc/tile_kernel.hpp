@@ -291,6 +291,16 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
   const int x0 = tile_bound(tx, w, nx), x1 = tile_bound(tx + 1, w, nx);
   const int P = x1 - x0 + 2 * (T - 1);
   const int y0 = tile_bound(ty, h, ny), y1 = tile_bound(ty + 1, h, ny);
+  // uniform coefficients, formed once
+  Medium<C, Th> um{};
+  if constexpr ((F & kPhiField) == 0) {
+    porous<Th>(k.phi_u, k, um);
+    if constexpr ((F & kHvField) == 0) exchange<Th>(k.hv_u * k.hvf, k, um);
+    if constexpr (sizeof(S) == 2)  // eight wavefronts a SIMD: no vector register to spare
+      for (C* v : {&um.rphi, &um.prp, &um.Fphi, &um.l0, &um.l1, &um.d0, &um.d1, &um.rD})
+        *v = __builtin_bit_cast(C, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, *v)));
+  }
+  const Medium<C, Th>* const uniform = (F & kPhiField) == 0 ? &um : nullptr;
   auto slot = [&](int x, int y) { return pops + (y - y0 + T - 1) * P + (x - x0 + T - 1); };
   // where step s (0, 1, ...) records this node: a node of the tile, once
   auto record = [&](int s, int x, int y) -> C* {
@@ -318,7 +328,7 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
       C* const rc = record(0, x, y);
       wrap(x, y);
       node_update_with<S, C, F>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk, step, rc,
-                                thermal_k<Th>(kk));
+                                thermal_k<Th>(kk), nullptr, uniform);
     });
   }
   __syncthreads();
@@ -342,7 +352,7 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
         const AaPull<S, C, N, true> pull{a, x, y, P};
         SinkPut<S, ScatterSink<S, N>> put{{a, P}};
         node_update_with<S, C, F & ~kRecord>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk,
-                                             step + 1u, nullptr, thermal_k<Th>(kk));
+                                             step + 1u, nullptr, thermal_k<Th>(kk), nullptr, uniform);
       }
       __syncthreads();
     }
@@ -354,7 +364,7 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
       const AaPull<S, C, N, true> pull{a, x, y, P};
       SinkPut<S, ScatterSink<S, N>> put{{a, P}};
       node_update_with<S, C, F | kInterior>(x, y, pull, put, phi_field, hv_field, nullptr, nullptr, nullptr, kk,
-                                            step + 1u, rc, thermal_k<Th>(kk));
+                                            step + 1u, rc, thermal_k<Th>(kk), nullptr, uniform);
     });
     __syncthreads();
   }
@@ -368,7 +378,7 @@ __device__ __forceinline__ void tile_body(const int tx, const int ty, const int 
       SinkPut<S, BufSink<S>> put{{d, (y - y0) * R + x * E, Q}};
       node_update_with<S, C, F | kMacrosIf>(x, y, pull, put, phi_field, hv_field, mac, nullptr, nullptr, kk,
                                             step + static_cast<uint32_t>(T - 1), record(T - 1, x, y),
-                                            thermal_k<Th>(kk));
+                                            thermal_k<Th>(kk), nullptr, uniform);
     });
   }
 }
