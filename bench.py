@@ -61,6 +61,7 @@ EXTRA = {"f32ext": dict(thermal_correction=1, pore_size=0.0135)}
 KERNEL_SOURCES = ["paper_1608_04118_amd/csrc/step_kernel.hpp", "paper_1608_04118_amd/csrc/step2_kernel.hpp",
                   "paper_1608_04118_amd/csrc/tile_kernel.hpp", "paper_1608_04118_amd/csrc/tile_launch.hpp",
                   "paper_1608_04118_amd/csrc/tile.hip", "paper_1608_04118_amd/csrc/tile_shapes.hip",
+                  "paper_1608_04118_amd/csrc/small_kernel.hpp",
                   "paper_1608_04118_amd/csrc/common.hpp",
                   "paper_1608_04118_amd/csrc/host_common.hpp", "paper_1608_04118_amd/csrc/lbm_ltne.hip",
                   "paper_1608_04118_amd/build.py"]

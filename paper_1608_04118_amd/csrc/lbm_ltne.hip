@@ -35,6 +35,7 @@ struct lbm_ltne {
   StepConsts<float> kf{};
   std::vector<double> tf0, ts0;  // initial temperature fields (if given), for the adjoint
   TileGrid tiles[2] = {};  // tiles of the launches of two and three steps
+  SmallTiles small{};      // tiles and steps of a small lattice's launches
   Staging staging;         // of lbm_ltne_macros
 
   void* pop(int i) const { return base + lay.off_pop[i]; }
@@ -138,12 +139,12 @@ hipError_t launch_step(const lbm_ltne* h, int mode, int64_t step, const void* sr
   }
 }
 
-
-// nsub (2 or 3) steps in one launch; with mac, the last one also writes the
-// macros (the last steps of a call); with rec, every step records q at the
-// interior nodes (5 planes a step).
-hipError_t launch_steps(const lbm_ltne* h, int nsub, int64_t step, const void* src, void* dst, void* mac,
-                        void* rec = nullptr, hipStream_t stream = nullptr) {
+// nsub steps in one launch, over the tiles of a small lattice or over those of
+// two and three steps; with mac, the last one also writes the macros (the last
+// steps of a call); with rec (not small), every step records q at the interior
+// nodes (5 planes a step).
+hipError_t launch_steps(const lbm_ltne* h, int nsub, bool small, int64_t step, const void* src, void* dst, void* mac,
+                        void* rec, hipStream_t stream) {
   TileLaunch a{};
   a.consts = compute_bytes(h->p.precision) == 8 ? static_cast<const void*>(&h->kd) : static_cast<const void*>(&h->kf);
   a.src = src;
@@ -152,14 +153,20 @@ hipError_t launch_steps(const lbm_ltne* h, int nsub, int64_t step, const void* s
   a.hv = h->hv();
   a.mac = mac;
   a.rec = rec;
-  a.grid = h->tiles[nsub - 2];
+  a.grid = small ? h->small.grid : h->tiles[nsub - 2];
   a.nsub = nsub;
   a.step = static_cast<uint32_t>(step);
   a.stream = stream ? stream : h->stream;
-  return launch_tiles(h->p.precision, a);
+  return small ? launch_small(h->p.precision, a) : launch_tiles(h->p.precision, a);
 }
 
-// Whether the lattice takes launches of several steps.
+// Tiles of the launches of two and three steps (a small lattice: recording
+// ones only).
+void choose_tiles(lbm_ltne* h) {
+  for (int nsub = 2; nsub <= kTileSteps; ++nsub) h->tiles[nsub - 2] = tile_grid(h->p, nsub);
+}
+
+// Whether the lattice takes launches of two and three steps.
 bool has_tiles(const lbm_ltne* h) { return h->tiles[0].ntiles > 0 && h->tiles[1].ntiles > 0; }
 
 // The next of `left` >= 1 steps (the first numbered step) in one launch, from
@@ -167,9 +174,16 @@ bool has_tiles(const lbm_ltne* h) { return h->tiles[0].ntiles > 0 && h->tiles[1]
 // or nullptr; rec: recorded sums, or nullptr.
 hipError_t launch_some(const lbm_ltne* h, int64_t left, int64_t step, const void* src, void* dst, void* mac, void* rec,
                        hipStream_t stream, int* nsub) {
-  *nsub = has_tiles(h) ? next_steps(left) : 1;
+  const bool small = h->small.steps > 0 && !rec && left > 1;
+  if (small) {
+    // as few launches as the steps need, of as even a length
+    const int64_t launches = (left + h->small.steps - 1) / h->small.steps;
+    *nsub = static_cast<int>((left + launches - 1) / launches);
+  } else {
+    *nsub = has_tiles(h) ? next_steps(left) : 1;
+  }
   void* const m = *nsub == left ? mac : nullptr;
-  if (*nsub > 1) return launch_steps(h, *nsub, step, src, dst, m, rec, stream);
+  if (*nsub > 1) return launch_steps(h, *nsub, small, step, src, dst, m, rec, stream);
   return launch_step(h, rec ? (m ? 4 : 3) : (m ? 1 : 0), step, src, dst, m, nullptr, nullptr, rec, stream);
 }
 
@@ -316,7 +330,8 @@ int lbm_ltne_create(const lbm_ltne_params* p, const double* phi_field, const dou
   }
   fill_consts(h, &h->kd);
   fill_consts(h, &h->kf);
-  for (int nsub = 2; nsub <= kTileSteps; ++nsub) h->tiles[nsub - 2] = tile_grid(h->p, nsub);
+  h->small = small_tiles(h->p);
+  if (h->small.steps == 0) choose_tiles(h);
 
   rc = LBM_OK;
   if (phi_field) rc = upload_field(h, phi_field, h->phi());
@@ -706,6 +721,8 @@ int adjoint_t(lbm_ltne* h, int64_t nsteps, int64_t K, double* loss, double* dphi
   R* wseed = reinterpret_cast<R*>(reinterpret_cast<char*>(ghv) + gb);
   R* itf = reinterpret_cast<R*>(reinterpret_cast<char*>(wseed) + fb);
   R* its = reinterpret_cast<R*>(reinterpret_cast<char*>(itf) + fb);
+
+  if (!has_tiles(h)) choose_tiles(h);
 
   // forward with checkpoints; the handle itself advances to t0 + nsteps.
   // The last nbuf segments are recorded on the way, into their buffers; the

@@ -1,9 +1,11 @@
-// The tiled kernels (two and three steps) of one precision form (LTNE_TILE_FORM, a value
-// of the precision field) and their launches.  Compiled once per form, with
+// The tiled kernels (two and three steps, and up to eight of a small lattice)
+// of one precision form (LTNE_TILE_FORM, a value of the precision field) and
+// their launches.  Compiled once per form, with
 // machine-level loop-invariant code motion off: the loop over a workgroup's
 // nodes would otherwise keep the binary64 literals of the node update in 46
 // vector registers across its iterations (152 registers instead of 110, two
 // wavefronts per SIMD instead of four).
+#include "small_kernel.hpp"
 #include "tile_kernel.hpp"
 
 namespace ltne {
@@ -52,6 +54,14 @@ void tiles_f(const TileLaunch& a) {
     tiles_ft<F, 2>(a);
 }
 
+template <int F>
+void small_f(const TileLaunch& a) {
+  hipLaunchKernelGGL((small_kernel<TS, TC, F>), dim3(kXcds * a.grid.per_xcd), dim3(SmallForm<TS, TC>::Block), 0, a.stream,
+                     *static_cast<const StepConsts<TC>*>(a.consts), static_cast<const TS*>(a.src),
+                     static_cast<TS*>(a.dst), static_cast<const TC*>(a.phi), static_cast<const TC*>(a.hv),
+                     static_cast<TC*>(a.mac), a.grid, a.nsub, a.step);
+}
+
 template <int F, int T>
 void batch_tiles_ft(const BatchTileLaunch& a) {
   const int per_xcd = (a.ntiles + kXcds - 1) / kXcds;
@@ -76,6 +86,16 @@ hipError_t LTNE_TILE_NAME(launch_tiles)(const TileLaunch& a) {
     case kPhiField: tiles_f<kPhiField>(a); break;
     case kHvField: tiles_f<kHvField>(a); break;
     default: tiles_f<kPhiField | kHvField>(a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t LTNE_TILE_NAME(launch_small)(const TileLaunch& a) {
+  switch ((a.phi ? kPhiField : 0) | (a.hv ? kHvField : 0)) {
+    case 0: small_f<0>(a); break;
+    case kPhiField: small_f<kPhiField>(a); break;
+    case kHvField: small_f<kHvField>(a); break;
+    default: small_f<kPhiField | kHvField>(a);
   }
   return hipGetLastError();
 }

@@ -1,7 +1,6 @@
-// Host interface of the tiled kernels of two or three steps (tile_kernel.hpp),
-// which are
-// compiled apart from the rest of the library (tile.hip, one object per
-// precision form).
+// Host interface of the tiled kernels (tile_kernel.hpp, small_kernel.hpp,
+// adjoint_tile.hpp), which are compiled apart from the rest of the library
+// (tile.hip, one object per precision form; adjoint_tile.hip).
 #pragma once
 
 #include "common.hpp"
@@ -55,6 +54,19 @@ struct TileGrid {
 // whose node update needs 80 to 128 registers, 8 with binary16 storage (64).
 inline int tile_slots(int precision) { return precision == LBM_FP64 ? 536 : (precision == LBM_FP16S ? 2144 : 1072); }
 
+// Threads of a workgroup of the small lattices' kernel, one a node of the tile
+// and its halo: two LDS buffers of 19 populations and the two fields in 160 KB.
+constexpr int small_slots(int storage_bytes, int compute_bytes) {
+  return storage_bytes == 8 ? 512 : (storage_bytes < compute_bytes && compute_bytes == 8 ? 960 : 1024);
+}
+// Most steps of its launches, and its tiles (steps = 0: the lattice is not small).
+constexpr int kSmallSteps = 8;
+struct SmallTiles {
+  TileGrid grid;
+  int steps;
+};
+SmallTiles small_tiles(const lbm_ltne_params& p);
+
 // The tile shape of one lattice's launches of nsub (2 or 3) steps.
 TileGrid tile_grid(const lbm_ltne_params& p, int nsub);
 // Tile shapes of a batch's lattices (all of them, or none: ntiles = 0).
@@ -77,6 +89,8 @@ struct TileLaunch {
   hipStream_t stream;
 };
 hipError_t launch_tiles(int precision, const TileLaunch& a);
+// The same for a small lattice (a.grid, a.nsub: small_tiles; no rec).
+hipError_t launch_small(int precision, const TileLaunch& a);
 
 struct BatchTileLaunch {
   char* base;
@@ -96,6 +110,10 @@ hipError_t launch_tiles_f64(const TileLaunch& a);
 hipError_t launch_tiles_f32(const TileLaunch& a);
 hipError_t launch_tiles_f16s(const TileLaunch& a);
 hipError_t launch_tiles_f32sr(const TileLaunch& a);
+hipError_t launch_small_f64(const TileLaunch& a);
+hipError_t launch_small_f32(const TileLaunch& a);
+hipError_t launch_small_f16s(const TileLaunch& a);
+hipError_t launch_small_f32sr(const TileLaunch& a);
 hipError_t launch_batch_tiles_f64(const BatchTileLaunch& a);
 hipError_t launch_batch_tiles_f32(const BatchTileLaunch& a);
 hipError_t launch_batch_tiles_f16s(const BatchTileLaunch& a);

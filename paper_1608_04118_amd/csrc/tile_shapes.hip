@@ -1,5 +1,5 @@
-// Tile shapes of the launches of two and three steps, chosen on the host, and the dispatch
-// over the precision forms.
+// Tile shapes of the launches of several steps, chosen on the host, and the
+// dispatch over the precision forms.
 #include <algorithm>
 #include <map>
 #include <utility>
@@ -97,6 +97,48 @@ TileGrid tile_grid(const lbm_ltne_params& p, int nsub) {
   return best_shape(p, nsub, tile_slots(p.precision), true);
 }
 
+// A lattice is small if at most 256 tiles, one a CU, cover it with at least
+// four steps a launch (512 nodes a workgroup with their halo in binary64, 960
+// to 1024 in the other forms): then every such launch measured beat three steps
+// over the larger kernel's tiles, from 48^2 (2.2 against 3.3 us a step in
+// binary64, 2.05 against 3.2 in binary32) to the largest (257 x 193 binary64
+// 3.4 against 4.0, 256^2 with three steps 4.14 against 4.17; 384^2 binary32 4.0
+// against 5.1).  Of the steps and shapes the one with the shortest predicted
+// step is taken: a launch takes fixed + T per_step + units per_unit us, where a
+// unit is a step's ceil(wavefronts / 4) on the CU's four SIMDs (fitted to 558
+// launches from 48^2 to 384^2, 2.8% rms, at most 9%).
+SmallTiles small_tiles(const lbm_ltne_params& p) {
+  // by precision: fixed, per step, per unit
+  static const double cost[4][3] = {{6.26, 0.46, 0.80}, {5.14, 0.73, 0.55}, {4.75, 1.12, 0.44}, {5.99, 0.54, 0.94}};
+  const double* c = cost[p.precision];
+  const int slots = small_slots(storage_bytes(p.precision), compute_bytes(p.precision));
+  SmallTiles best{};
+  if (static_cast<long long>(p.nx) * p.ny > static_cast<long long>(kCus) * slots) return best;
+  double least = 0.0;
+  // a halo wraps round a periodic axis once
+  const int tmax = std::min({kSmallSteps, p.periodic_x ? p.nx : kSmallSteps, p.periodic_y ? p.ny : kSmallSteps});
+  for (int T = 4; T <= tmax; ++T) {
+    for (int ntx = 1; ntx <= kCus; ++ntx) {
+      const int w = std::max(4, ceil_div(p.nx, ntx));
+      const int nty = kCus / ceil_div(p.nx, w);
+      const int h = std::max(4, ceil_div(p.ny, nty));
+      if (w + 2 * T <= slots / (4 + 2 * T) && (w + 2 * T) * (h + 2 * T) <= slots) {
+        int units = 0;
+        for (int g = 0; g < T; ++g)
+          units += ceil_div(waves(std::min(w + 2 * g, p.nx) * std::min(h + 2 * g, p.ny)), 4);
+        const double us = (c[0] + T * c[1] + units * c[2]) / T;
+        if (best.steps == 0 || us < least) {
+          best.grid = grid_of(p, w, h);
+          best.steps = T;
+          least = us;
+        }
+      }
+      if (w == 4) break;
+    }
+  }
+  return best;
+}
+
 TileGrid adjoint_tile_grid(const lbm_ltne_params& p, int slots) { return best_shape(p, 2, slots, true); }
 
 // A batch: each lattice takes the shape with the fewest passes in all; the
@@ -137,6 +179,15 @@ hipError_t launch_tiles(int precision, const TileLaunch& a) {
     case LBM_FP32: return launch_tiles_f32(a);
     case LBM_FP16S: return launch_tiles_f16s(a);
     default: return launch_tiles_f32sr(a);
+  }
+}
+
+hipError_t launch_small(int precision, const TileLaunch& a) {
+  switch (precision) {
+    case LBM_FP64: return launch_small_f64(a);
+    case LBM_FP32: return launch_small_f32(a);
+    case LBM_FP16S: return launch_small_f16s(a);
+    default: return launch_small_f32sr(a);
   }
 }
 

@@ -55,6 +55,29 @@ def test_tiles_equal_single_steps(B, form, size):
         many.close()
 
 
+# one workgroup, tiles of a node's halo across both ends of an axis, the
+# longest halo a periodic axis takes, the largest lattices of the rule, the
+# first beyond it
+SMALL = [(8, 8, 1, 1), (7, 40, 1, 0), (40, 5, 0, 1), (64, 64, 0, 0), (100, 37, 1, 1), (192, 191, 0, 0),
+         (257, 193, 0, 0), (384, 384, 1, 0), (386, 385, 0, 0)]
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("size", SMALL, ids=lambda s: "%dx%d_p%d%d" % s)
+def test_small_lattices_equal_single_steps(B, form, size):
+    p, phi, hv, tf, ts = _case(*size, FORMS[form])
+    for fields in (dict(phi=phi, Hv=hv, Tf0=tf, Ts0=ts), dict(Tf0=tf, Ts0=ts), dict(phi=phi), dict(Hv=hv)):
+        one, many = B.Lattice(p, **fields), B.Lattice(p, **fields)
+        for calls in ((8, 7), (9,), (25,), (4,)):  # 8, 7; 5 + 4; 7 + 6 + 6 + 6; 4 (of eight)
+            for n in calls:
+                many.step(n)
+            for _ in range(sum(calls)):
+                one.step(1)
+            _same(one.macros(), many.macros())
+        one.close()
+        many.close()
+
+
 @pytest.mark.parametrize("form", FORMS)
 def test_batch_tiles_equal_single_lattices(B, form):
     cases = [_case(*s, FORMS[form]) for s in SIZES]
