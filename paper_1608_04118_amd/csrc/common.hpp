@@ -136,6 +136,7 @@ struct StepConsts {
   C inv_sigma;           // (rho c_p)_f / (rho c_p)_s
   C Qf, Qs;              // heat sources (Eq. 45)
   C s_e, s_eps, s_q, s_nu;
+  C h_e, h_eps, h_q, h_nu;  // 1 - s / 2 of each
   C z_a, z_e, z_nu;      // fluid D2Q5 rates (Eq. 39)
   C e_a, e_e, e_nu;      // solid D2Q5 rates (Eq. 40)
   C varpi;

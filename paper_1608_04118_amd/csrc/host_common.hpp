@@ -149,6 +149,10 @@ inline void fill_step_consts(const lbm_ltne_params& p, const lbm_ltne_derived& d
   k->s_eps = static_cast<C>(p.s_eps);
   k->s_q = static_cast<C>(p.s_q);
   k->s_nu = static_cast<C>(d.s_nu);
+  k->h_e = C(1) - C(0.5) * k->s_e;
+  k->h_eps = C(1) - C(0.5) * k->s_eps;
+  k->h_q = C(1) - C(0.5) * k->s_q;
+  k->h_nu = C(1) - C(0.5) * k->s_nu;
   k->z_a = static_cast<C>(d.zeta_a);
   k->z_e = static_cast<C>(p.zeta_e);
   k->z_nu = static_cast<C>(p.zeta_nu);

@@ -672,13 +672,20 @@ __device__ __forceinline__ void node_update_with(
     const C S1 = C(6) * uF;
     const C S7 = C(2) * (ux * rFx - uy * rFy) * ip;
     const C S8 = (ux * rFy + uy * rFx) * ip;
+    // 1 - s / 2: from the host, but with binary16 storage, where one more
+    // scalar load costs more than the instruction (64^2 binary64 2.14 to 2.08 us
+    // a step, 192^2 3.52 to 3.44, 4096^2 binary32 248.4 to 246.1, but binary16
+    // 3072 x 2048 79.6 to 81.1)
+    constexpr bool narrow = sizeof(S) == 2;
+    const C h_e = narrow ? C(1) - C(0.5) * k.s_e : k.h_e, h_eps = narrow ? C(1) - C(0.5) * k.s_eps : k.h_eps;
+    const C h_q = narrow ? C(1) - C(0.5) * k.s_q : k.h_q, h_nu = narrow ? C(1) - C(0.5) * k.s_nu : k.h_nu;
     const C ms0 = drho;
-    const C ms1 = m1 - k.s_e * (m1 - meq1) + (C(1) - C(0.5) * k.s_e) * S1;
-    const C ms2 = m2 - k.s_eps * (m2 - meq2) - (C(1) - C(0.5) * k.s_eps) * S1;
-    const C ms4 = m4 - k.s_q * (m4 + jxr) - (C(1) - C(0.5) * k.s_q) * rFx;
-    const C ms6 = m6 - k.s_q * (m6 + jyr) - (C(1) - C(0.5) * k.s_q) * rFy;
-    const C ms7 = m7 - k.s_nu * (m7 - meq7) + (C(1) - C(0.5) * k.s_nu) * S7;
-    const C ms8 = m8 - k.s_nu * (m8 - meq8) + (C(1) - C(0.5) * k.s_nu) * S8;
+    const C ms1 = m1 - k.s_e * (m1 - meq1) + h_e * S1;
+    const C ms2 = m2 - k.s_eps * (m2 - meq2) - h_eps * S1;
+    const C ms4 = m4 - k.s_q * (m4 + jxr) - h_q * rFx;
+    const C ms6 = m6 - k.s_q * (m6 + jyr) - h_q * rFy;
+    const C ms7 = m7 - k.s_nu * (m7 - meq7) + h_nu * S7;
+    const C ms8 = m8 - k.s_nu * (m8 - meq8) + h_nu * S8;
     // f* = M^{-1} m*, M^{-1} = M^T diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4)
     const C a = ms0 * (C(1) / C(9));
     const C b = ms1 * (C(1) / C(36));
@@ -736,7 +743,14 @@ __device__ __forceinline__ void node_update_with(
     const T nf1 = a1 - a3, nf2 = a2 - a4;
     const T nf3 = T(-4) * a0 + ((a1 + a2) + (a3 + a4));
     const T nf4 = (a1 - a2) + (a3 - a4);
-    const T tx = kt.z_a * (nf1 - qx) - tcf * T(rFx), ty = kt.z_a * (nf2 - qy) - tcf * T(rFy);
+    T tx, ty;
+    if (sizeof(S) == 2 && kt.tc == T(0)) {  // (81.6 to 80.9; binary32 at 1024^2 16.6 to 17.0)
+      tx = kt.z_a * (nf1 - qx);
+      ty = kt.z_a * (nf2 - qy);
+    } else {
+      tx = kt.z_a * (nf1 - qx) - tcf * T(rFx);
+      ty = kt.z_a * (nf2 - qy) - tcf * T(rFy);
+    }
     const T u3 = nf3 - kt.c1 * thf;
     T f4o;  // its last population, stored with the solid lattice's first
     S f4;   // the same, rounded (FP32 form)
