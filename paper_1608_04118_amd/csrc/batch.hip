@@ -417,7 +417,11 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
     int parity = b->parity;
     uint32_t step0 = static_cast<uint32_t>(b->steps + 1);
     void* args[] = {&base, &cav, &ks, &tiles, &ntiles, &nsteps, &parity, &macros_last, &ctl, &spin, &step0};
-    HIP_TRY(hipLaunchCooperativeKernel(fn, dim3(b->grid), dim3(kBlock), args, 0, b->stream));
+    // no workgroup without a tile: the barrier needs every workgroup resident,
+    // and a grid that fills every CU to the last register leaves no room for
+    // one whose registers do not fall into one piece
+    const int grid = std::min(b->grid, (ntiles + kXcds - 1) / kXcds * kXcds);
+    HIP_TRY(hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kBlock), args, 0, b->stream));
     b->parity = (b->parity + nsteps) & 1;
   } else {
     const int per = (ntiles + kXcds - 1) / kXcds;
