@@ -17,6 +17,7 @@
 #include <atomic>
 #include <cstring>
 #include <exception>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -35,6 +36,10 @@ constexpr long long kChunk = 262144;
 // Output bytes that pay for one more thread (starting it takes about 12 us).
 constexpr long long kBytesPerThread = 4LL << 20;
 constexpr int kMaxThreads = 8;
+// Fields up to this size are not worth pinned memory of their own: getting and
+// freeing it takes 50 us, and a pageable copy reads 160 KB in 24 us against 23,
+// 500 KB in 50 against 43.
+constexpr size_t kPageable = 512 << 10;
 
 struct Run {  // `count` values from value `at` of the fields on
   long long at, count;
@@ -168,6 +173,14 @@ hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* 
   if (nruns == 0) return hipSuccess;
   const int nslots = std::min(nruns, Staging::kSlots);
   const size_t slot = static_cast<size_t>(nruns == 1 ? runs[0].count : kChunk) * elem;
+  if (nruns == 1 && slot <= kPageable && st.bytes < slot) {
+    std::unique_ptr<char[]> tmp(new (std::nothrow) char[slot]);
+    if (!tmp) return hipErrorOutOfMemory;
+    hipError_t e = hipMemcpyAsync(tmp.get(), src + runs[0].at * elem, slot, hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e == hipSuccess) deliver(tmp.get(), runs[0], elem, n, outs, true);
+    return e;
+  }
   if (reserve(st, device, slot * nslots, nslots) != hipSuccess) {
     (void)hipGetLastError();
     return read_pageable(stream, src, elem, n, outs);
