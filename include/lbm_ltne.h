@@ -181,10 +181,10 @@ int lbm_ltne_create(const lbm_ltne_params *p, const double *phi_field, const dou
 
 /* Advances nsteps >= 0 time steps (asynchronous).  A step is fused: pull
  * streaming, wall reconstruction, macros, the three collisions, store.  A
- * launch advances three steps (two where that leaves no single step over)
- * with the time levels between kept on chip; a single step left over, the
- * steps checked under diag_every, and the steps of lattices with rows of
- * 200 MB and more run alone.  The result equals single steps bit for bit.
+ * launch advances three steps (two where that leaves no single step over),
+ * on small lattices up to eight, with the time levels between kept on chip; a
+ * single step left over, the steps checked under diag_every, and the steps of
+ * lattices with rows of 200 MB and more run alone.  The result equals single steps bit for bit.
  * The macros of the last step are kept for
  * lbm_ltne_macros, lbm_ltne_nusselt and lbm_ltne_diagnostics; the residual
  * compares them with the macros kept by the previous call that advanced the

@@ -17,9 +17,9 @@
 // us a step with tiles dealt over the XCDs, 3.2 this way).
 // Measured against launches of three steps (tile_kernel), us per step:
 //            binary64     binary32     binary16     f32sr
-//    64^2   3.30  2.24   3.16  2.04   3.63  2.24   3.79  2.39
-//   128^2   3.24  2.45   3.02  2.18   3.38  2.35   3.55  2.59
-//   192^2   3.65  2.96   3.25  2.41   3.52  2.52   3.71  3.06
+//    64^2   3.30  2.09   3.16  2.07   3.63  2.24   3.79  2.39
+//   128^2   3.24  2.31   3.02  2.16   3.38  2.35   3.55  2.59
+//   192^2   3.65  2.85   3.25  2.41   3.52  2.52   3.71  2.99
 //   256^2    --    --    3.55  2.79   3.79  2.84   4.30  3.64
 //   320^2    --    --    4.20  3.21   4.20  3.27   5.07  4.34
 #pragma once

@@ -20,18 +20,21 @@
 // (binary32) and one (binary64) per SIMD.  With two steps the memory still
 // takes as long as the arithmetic (binary64: a workgroup's loads and stores
 // fill 13.9 of its 14.2 us at its CU's share of the bandwidth); with three the
-// halo costs 6% (binary32) to 13% (binary64) more arithmetic, and vector
-// instructions take most of the cycles (85% and 76%, at the rates above).
+// halo costs 6% (binary32) to 13% (binary64) more arithmetic.  Then vector
+// instructions take 80% of the time in binary32, at the rates above, and 60% in
+// binary64, where the 26.9 GB that a launch moves at 8192^2 take the rest: the
+// halo and the tile rows that end inside cache lines add 28% to what it must
+// move (4.9 TB/s, a plain copy's rate).
 // Measured, us per step of a porous layer (one box for each row but the
 // register window's):
 //                    one step  register window  two steps  three steps
-//   4096^2 binary32     434          341            305        275
-//   4096^2 binary64     869          619            566        464
-//   4096^2 f32sr        510           --            399        390
-//   4096^2 binary16     271           --            235        228
-//   1024^2 binary32     28.6         32.5          19.6       18.6
+//   4096^2 binary32     434          341            305        251
+//   4096^2 binary64     869          619            566        446
+//   4096^2 f32sr        510           --            399        371
+//   4096^2 binary16     271           --            235        210
+//   1024^2 binary32     28.6         32.5          19.6       18.0
 //   1024^2 binary64     52.4         61.3          38.7       32.2
-//    512^2 binary64     15.7         21.0          10.2        9.5
+//    512^2 binary64     15.7         21.0          10.2        8.9
 #pragma once
 
 #include "step_kernel.hpp"

@@ -80,12 +80,14 @@ TileGrid best_shape(const lbm_ltne_params& p, int nsub, int slots, bool per_cu) 
 }  // namespace
 
 // Large lattices (2048 tiles and more, eight per CU) take the shape that ran
-// fastest on the 4096^2 layer (us per step, three steps: binary32 48 x 16: 275,
-// 28 x 28: 279, 64 x 11: 280; binary64 24 x 15: 464, 19 x 19: 474, 60 x 4: 537;
-// f32sr 48 x 16: 390, 28 x 28: 398; binary16 54 x 30: 228, 62 x 24: 230).  On
-// smaller ones a launch takes 4.2 us plus 0.23 us (binary32) times the passes
-// of the busiest CU, which holds ceil(tiles / 256) tiles (two steps, checked
-// from 257 x 193 to 1024^2 within 3%): that product is made smallest.
+// fastest on a layer (us per step, three steps: 4096^2 binary32 48 x 16: 251,
+// 32 x 24: 255, 64 x 11: 255, 28 x 28: 260; 4096 x 2048 binary64 24 x 15: 225,
+// 32 x 10: 232, 20 x 18: 233, 16 x 22: 241; 3072^2 f32sr 48 x 16: 210,
+// 32 x 24: 208, 64 x 11: 216; 3072 x 2048 binary16 54 x 30: 82, 64 x 26: 82,
+// 32 x 52: 84).  On smaller ones a launch takes 4.2 us plus 0.23 us (binary32)
+// times the passes of the busiest CU, which holds ceil(tiles / 256) tiles (two
+// steps, checked from 257 x 193 to 1024^2 within 3%): that product is made
+// smallest.
 TileGrid tile_grid(const lbm_ltne_params& p, int nsub) {
   // by steps and precision
   static const int wide[2][4][2] = {{{32, 13}, {64, 14}, {62, 24}, {48, 16}}, {{24, 15}, {48, 16}, {54, 30}, {48, 16}}};
