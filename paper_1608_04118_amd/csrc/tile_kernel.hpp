@@ -22,9 +22,8 @@
 // fill 13.9 of its 14.2 us at its CU's share of the bandwidth); with three the
 // halo costs 6% (binary32) to 13% (binary64) more arithmetic.  Then vector
 // instructions take 80% of the time in binary32, at the rates above, and 60% in
-// binary64, where the 26.9 GB that a launch moves at 8192^2 take the rest: the
-// halo and the tile rows that end inside cache lines add 28% to what it must
-// move (4.9 TB/s, a plain copy's rate).
+// binary64, where the 24.1 GB that a launch moves at 8192^2 (20.9 and the halo)
+// come at 4.4 TB/s, against 4.9 of a plain copy.
 // Measured, us per step of a porous layer (one box for each row but the
 // register window's):
 //                    one step  register window  two steps  three steps
