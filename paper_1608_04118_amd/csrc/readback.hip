@@ -129,7 +129,16 @@ hipError_t reserve(Staging& st, int device, size_t bytes, int nslots) {
   return e;
 }
 
-// Without staging memory: one pageable copy per field.
+// Whether two fields go to overlapping arrays: then they are delivered one
+// after the other, so that what is left there is the last field's.
+bool overlapping(long long n, double* const outs[5]) {
+  for (int f = 0; f < 5; ++f)
+    for (int g = 0; g < f; ++g)
+      if (outs[f] && outs[g] && outs[f] < outs[g] + n && outs[g] < outs[f] + n) return true;
+  return false;
+}
+
+// One pageable copy per field, in their order.
 hipError_t read_pageable(hipStream_t stream, const char* src, int elem, long long n, double* const outs[5]) {
   for (int f = 0; f < 5; ++f) {
     if (!outs[f]) continue;
@@ -161,6 +170,7 @@ void Staging::release() {
 hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* src_, int elem, long long n,
                        double* const outs[5]) {
   const char* const src = static_cast<const char*>(src_);
+  if (overlapping(n, outs)) return read_pageable(stream, src, elem, n, outs);
   std::vector<Run> runs;
   std::vector<std::thread> threads;
   try {

@@ -27,6 +27,7 @@ struct Staging {
 // Copies the five fields of n values of elem bytes (4 or 8) that lie one
 // after another at device address src to the host arrays outs (nullptr: left
 // out), as doubles, after the work on the stream; returns when they are there.
+// Arrays that overlap hold the last of their fields, in the order of outs.
 // device: the stream's.
 hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* src, int elem, long long n,
                        double* const outs[5]);
