@@ -651,15 +651,17 @@ int lbm_ltne_batch_step(lbm_ltne_batch_t b, int64_t nsteps) {
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
   if (nsteps < 0) return set_error(LBM_EINVAL, "nsteps < 0");
   if (nsteps == 0) return LBM_OK;
-  // one persistent launch covers up to 2^20 steps; longer runs are split
+  // one persistent launch covers up to 2^20 steps; longer runs are split (the
+  // launches number their steps, which seed the stochastic rounding, from
+  // b->steps on)
   int64_t left = nsteps;
   while (left > 0) {
     const int chunk = static_cast<int>(std::min<int64_t>(left, 1 << 20));
     const int rc = launch_batch(b, chunk, left == chunk ? 1 : 0);
     if (rc != LBM_OK) return rc;
+    b->steps += chunk;
     left -= chunk;
   }
-  b->steps += nsteps;
   return LBM_OK;
 }
 
