@@ -234,8 +234,8 @@ struct lbm_ltne_batch {
   int parity = 0;     // buffer holding the current state
   int64_t steps = 0;
   int persistent = 0; // 1: cooperative persistent launch, 0: one launch per step (default, faster)
-  int grid = 0;       // workgroups of the persistent launch
-  int grid2 = 0;      // workgroups of the persistent two-step launch (FP32)
+  int grid = 0;       // most workgroups of the persistent launch
+  int grid2 = 0;      // most workgroups of the persistent two-step launch (FP32)
   size_t consts_bytes = 0, desc_bytes = 0;
   long long nodes = 0;
   Staging staging;  // of lbm_ltne_batch_macros
@@ -332,16 +332,22 @@ const void* batch2p_function(const lbm_ltne_batch* b) {
   }
 }
 
-// Workgroups that can be resident at once (multiple of 8), for the
-// cooperative launch.
+// Most workgroups of a persistent launch (a multiple of 8).  The grid barrier
+// needs every one of them resident, so the grid stays below what the occupancy
+// calculation says the chip holds: by one workgroup a CU where a CU holds
+// several, by one CU per XCD where it holds one.  A grid that filled every CU
+// (1792 workgroups of the binary16 kernel, seven wavefronts of 72 registers
+// each on a SIMD's 512) once ended in the barrier's bounded wait; why is not
+// known, and a workgroup that found no room is the likeliest reason.
 int resident_grid(const lbm_ltne_batch* b, int* out, const void* fn = nullptr, int block = kBlock) {
   int per_cu = 0;
   HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn ? fn : batch_function(b), block, 0));
   hipDeviceProp_t prop;
   HIP_TRY(hipGetDeviceProperties(&prop, b->device));
-  int g = per_cu * prop.multiProcessorCount;
+  const int cus = prop.multiProcessorCount;
+  int g = per_cu > 1 ? (per_cu - 1) * cus : per_cu * (cus - kXcds);
   g -= g % kXcds;
-  *out = g;
+  *out = std::max(g, 0);
   return LBM_OK;
 }
 
@@ -371,6 +377,16 @@ bool persist_pairs_ok(const lbm_ltne_batch* b) {
   return b->precision == LBM_FP32 && b->step2_addr && b->nwaves2_min >= kPersistMinWaves;
 }
 
+// Workgroups of the persistent launch that a call runs (pairs: of the one with
+// pairs of steps): none without a tile, or without an item of work for each of
+// its wavefronts in its XCD's share.
+int persist_grid(const lbm_ltne_batch* b, bool pairs) {
+  auto share = [](int n) { return (n + kXcds - 1) / kXcds; };
+  constexpr int waves = kPersistBlock / 64;
+  return pairs ? std::min(b->grid2, kXcds * ((share(b->nwaves2) + waves - 1) / waves))
+               : std::min(b->grid, kXcds * share(b->ntiles));
+}
+
 // nsteps steps of every lattice.  Per-step mode: three steps a launch, two
 // where that leaves no single step over (two_step), a single step alone; the
 // last launch writes the macros (macros_last).  The
@@ -397,8 +413,8 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
       int nw = b->nwaves2;
       uint32_t step0 = static_cast<uint32_t>(b->steps + 1);
       void* args[] = {&base, &cav, &ks, &waves, &nw, &npairs, &parity, &ctl, &spin, &step0};
-      HIP_TRY(hipLaunchCooperativeKernel(batch2p_function(b), dim3(b->grid2), dim3(kPersistBlock), args, 0,
-                                         b->stream));
+      HIP_TRY(hipLaunchCooperativeKernel(batch2p_function(b), dim3(persist_grid(b, true)), dim3(kPersistBlock),
+                                         args, 0, b->stream));
       parity = (parity + npairs) & 1;
     }
     const int per = (ntiles + kXcds - 1) / kXcds;
@@ -417,11 +433,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
     int parity = b->parity;
     uint32_t step0 = static_cast<uint32_t>(b->steps + 1);
     void* args[] = {&base, &cav, &ks, &tiles, &ntiles, &nsteps, &parity, &macros_last, &ctl, &spin, &step0};
-    // no workgroup without a tile: the barrier needs every workgroup resident,
-    // and a grid that fills every CU to the last register leaves no room for
-    // one whose registers do not fall into one piece
-    const int grid = std::min(b->grid, (ntiles + kXcds - 1) / kXcds * kXcds);
-    HIP_TRY(hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kBlock), args, 0, b->stream));
+    HIP_TRY(hipLaunchCooperativeKernel(fn, dim3(persist_grid(b, false)), dim3(kBlock), args, 0, b->stream));
     b->parity = (b->parity + nsteps) & 1;
   } else {
     const int per = (ntiles + kXcds - 1) / kXcds;
@@ -678,7 +690,7 @@ int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t* nodes, int32_t* tiles, int3
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
   if (nodes) *nodes = b->nodes;
   if (tiles) *tiles = b->ntiles;
-  if (grid) *grid = persist_pairs_ok(b) ? b->grid2 : b->grid;
+  if (grid) *grid = persist_grid(b, persist_pairs_ok(b));
   if (persistent) *persistent = b->persistent;
   return LBM_OK;
 }
