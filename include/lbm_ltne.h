@@ -286,6 +286,11 @@ int lbm_ltne_batch_nusselt(lbm_ltne_batch_t b, int32_t i, double *Nu_f, double *
 /* 0: one launch per step (default), 1: persistent cooperative launch (LBM_EUNSUPPORTED if the
  * device cannot keep a grid resident). */
 int lbm_ltne_batch_set_mode(lbm_ltne_batch_t b, int32_t persistent);
+/* Polls after which a barrier wait of the persistent launch gives up (0: the
+ * default, about 10 s).  The launch then ends early and the batch's state is
+ * lost, which the next synchronizing call reports as LBM_EHIP; the autotuner
+ * restores the state and does without the mode. */
+int lbm_ltne_batch_set_spin_limit(lbm_ltne_batch_t b, uint32_t polls);
 /* Total nodes, tiles, persistent grid size (workgroups) and current mode. */
 int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t *nodes, int32_t *tiles, int32_t *grid,
                         int32_t *persistent);
@@ -301,7 +306,7 @@ int lbm_ltne_batch_get_chunks(lbm_ltne_batch_t b, int32_t *rows);
  * persistent launch runs pairs of steps) chunk heights 8..32 by timing 6 reps
  * steps of that launch, then the launch mode (launches of several steps, or
  * one persistent launch; skipped when the device has no resident
- * grid for it) by timing 6 reps steps of each, every trial from a snapshot
+ * grid for it, not taken where one of its barriers times out) by timing 6 reps steps of each, every trial from a snapshot
  * of the state (restored afterwards), and keeps the fastest of each;
  * ms_per_step (may be NULL) receives the time per step of the chosen
  * configuration on the path the batch runs (launches of several steps where they

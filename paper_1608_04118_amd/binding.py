@@ -102,6 +102,7 @@ def lib():
             "lbm_ltne_batch_macros": ([vp, i32, vp, vp, vp, vp, vp], C.c_int),
             "lbm_ltne_batch_nusselt": ([vp, i32, dp, dp], C.c_int),
             "lbm_ltne_batch_set_mode": ([vp, i32], C.c_int),
+            "lbm_ltne_batch_set_spin_limit": ([vp, C.c_uint32], C.c_int),
             "lbm_ltne_batch_info": ([vp, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32),
                                      C.POINTER(i32)], C.c_int),
             "lbm_ltne_batch_set_tiles": ([vp, vp], C.c_int),
@@ -487,6 +488,10 @@ def lbm_ltne_batch_set_mode(b, persistent):
     _check(lib().lbm_ltne_batch_set_mode(b, int(persistent)), "lbm_ltne_batch_set_mode")
 
 
+def lbm_ltne_batch_set_spin_limit(b, polls):
+    _check(lib().lbm_ltne_batch_set_spin_limit(b, int(polls)), "lbm_ltne_batch_set_spin_limit")
+
+
 def lbm_ltne_batch_info(b):
     n, t, g, m = C.c_int64(), C.c_int32(), C.c_int32(), C.c_int32()
     _check(lib().lbm_ltne_batch_info(b, C.byref(n), C.byref(t), C.byref(g), C.byref(m)),
@@ -556,6 +561,10 @@ class Batch:
 
     def set_mode(self, persistent):
         lbm_ltne_batch_set_mode(self.h, persistent)
+
+    def set_spin_limit(self, polls):
+        """Polls after which a barrier wait of the persistent launch gives up."""
+        lbm_ltne_batch_set_spin_limit(self.h, polls)
 
     def info(self):
         return lbm_ltne_batch_info(self.h)

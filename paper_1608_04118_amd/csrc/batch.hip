@@ -210,6 +210,10 @@ __global__ __launch_bounds__(kPersistBlock) void batch2p_kernel(
 
 using namespace ltne;
 
+namespace {
+constexpr unsigned kSpinLimit = 1u << 24;  // about 10 s
+}
+
 struct lbm_ltne_batch {
   int n = 0;
   int precision = LBM_FP32;
@@ -240,6 +244,7 @@ struct lbm_ltne_batch {
   long long nodes = 0;
   Staging staging;  // of lbm_ltne_batch_macros
   bool barriers = false;  // a persistent launch was queued, so ctl may hold a timeout
+  unsigned spin_limit = kSpinLimit;  // polls of a barrier wait of the persistent launch
 
   long long n_of(int i) const { return static_cast<long long>(p[i].nx) * p[i].ny; }
 };
@@ -351,8 +356,6 @@ int resident_grid(const lbm_ltne_batch* b, int* out, const void* fn = nullptr, i
   return LBM_OK;
 }
 
-constexpr unsigned kSpinLimit = 1u << 24;
-
 // A launch of nsub (2 or 3) steps over every lattice; macros: the last step
 // also writes the macros.
 hipError_t launch_batch_steps(const lbm_ltne_batch* b, int nsub, int parity, uint32_t step, bool macros) {
@@ -400,7 +403,7 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
   const void* tiles = b->base + b->off_tiles;
   BatchCtl* ctl = reinterpret_cast<BatchCtl*>(b->base + b->off_ctl);
   int ntiles = b->ntiles;
-  unsigned spin = kSpinLimit;
+  unsigned spin = b->spin_limit;
   if (b->persistent && two_step && persist_pairs_ok(b)) {
     // the pairs of steps in one persistent launch, then the remaining single
     // step (the one that writes the macros) as an ordinary launch
@@ -461,11 +464,20 @@ int launch_batch(lbm_ltne_batch* b, int nsteps, int macros_last, bool two_step =
   return LBM_OK;
 }
 
-int check_ctl(lbm_ltne_batch* b) {
+// Whether a barrier of the last persistent launch timed out.
+int read_ctl(lbm_ltne_batch* b, bool* timeout) {
   BatchCtl c;
   HIP_TRY(hipMemcpyAsync(&c, b->base + b->off_ctl, sizeof(c), hipMemcpyDeviceToHost, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));
-  if (c.error) return set_error(LBM_EHIP, "a grid barrier of the persistent batch launch timed out");
+  *timeout = c.error != 0;
+  return LBM_OK;
+}
+
+int check_ctl(lbm_ltne_batch* b) {
+  bool timeout = false;
+  const int rc = read_ctl(b, &timeout);
+  if (rc != LBM_OK) return rc;
+  if (timeout) return set_error(LBM_EHIP, "a grid barrier of the persistent batch launch timed out");
   return LBM_OK;
 }
 
@@ -685,6 +697,12 @@ int lbm_ltne_batch_set_mode(lbm_ltne_batch_t b, int32_t persistent) {
   return LBM_OK;
 }
 
+int lbm_ltne_batch_set_spin_limit(lbm_ltne_batch_t b, uint32_t polls) {
+  if (!b) return set_error(LBM_EINVAL, "batch is NULL");
+  b->spin_limit = polls ? polls : kSpinLimit;
+  return LBM_OK;
+}
+
 int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t* nodes, int32_t* tiles, int32_t* grid,
                         int32_t* persistent) {
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
@@ -731,6 +749,10 @@ int lbm_ltne_batch_get_chunks(lbm_ltne_batch_t b, int32_t* rows) {
 int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_step) {
   if (!b) return set_error(LBM_EINVAL, "batch is NULL");
   if (reps <= 0) reps = 4;
+  if (b->barriers) {  // a state lost before this call is no state to restore
+    const int lost = check_ctl(b);
+    if (lost != LBM_OK) return lost;
+  }
   // Snapshot the state: trial steps must not advance the simulation.
   size_t pop_total = 0;
   for (int i = 0; i < b->n; ++i) pop_total += b->off_pop1[i] - b->off_pop0[i];
@@ -756,6 +778,21 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     return set_error(LBM_EHIP, "event creation failed");
   }
   const int parity0 = b->parity;
+  constexpr float kNever = 1e30f;
+  bool can_persist = b->grid >= kXcds && !(b->precision == LBM_FP32 && b->grid2 < kXcds);
+  // After a trial: where a barrier of a persistent launch timed out, the batch
+  // does without that mode (what the steps left is replaced by the snapshot).
+  auto settle = [&](float* ms) -> int {
+    bool timeout = false;
+    int r = b->barriers ? read_ctl(b, &timeout) : LBM_OK;
+    if (r != LBM_OK || !timeout) return r;
+    can_persist = false;
+    b->persistent = 0;
+    *ms = kNever;
+    HIP_TRY(hipMemsetAsync(b->base + b->off_ctl, 0, sizeof(BatchCtl), b->stream));
+    HIP_TRY(hipStreamSynchronize(b->stream));
+    return LBM_OK;
+  };
   auto trial = [&](float* ms) -> int {
     int rc = copy_state(false);
     if (rc != LBM_OK) return rc;
@@ -768,10 +805,9 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
-    rc = check_ctl(b);
     *ms /= static_cast<float>(reps);
     b->parity = parity0;
-    return rc;
+    return settle(ms);
   };
   int rc = copy_state(true);
   if (rc == LBM_OK) rc = (hipStreamSynchronize(b->stream) == hipSuccess) ? LBM_OK : LBM_EHIP;
@@ -817,21 +853,19 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
-    r = check_ctl(b);
     *ms /= static_cast<float>(6 * reps);
     b->parity = parity0;
-    return r;
+    return settle(ms);
   };
   if (rc == LBM_OK) rc = upload_tables(b);
   // The chunk heights of the persistent two-step launch (FP32 form).
-  const bool can_persist = b->grid >= kXcds && !(b->precision == LBM_FP32 && b->grid2 < kXcds);
   if (rc == LBM_OK && can_persist && persist_pairs_ok(b)) {
     rc = trial2(1, &best);
     for (auto& kv : classes) {
       if (rc != LBM_OK) break;
       int best_rows = b->rows2[kv.second[0]];
       for (int r : kBatch2RowChoices) {
-        if (r == best_rows) continue;
+        if (r == best_rows || !can_persist) continue;
         for (int i : kv.second) b->rows2[i] = r;
         rc = upload_tables(b);
         float ms = 0.0f;
@@ -850,16 +884,16 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
   // runs; the faster is kept.  Persistent launches pay off where launches are
   // a large part of a step (small batches).
   if (rc == LBM_OK) {
-    float ms_mode[2] = {0.0f, 0.0f};
+    float ms_mode[2] = {0.0f, kNever};
     for (int m = 0; m < (can_persist ? 2 : 1) && rc == LBM_OK; ++m) rc = trial2(m, &ms_mode[m]);
     b->persistent = can_persist && ms_mode[1] < ms_mode[0] ? 1 : 0;
     best = ms_mode[b->persistent];
   }
   if (rc != LBM_OK) b->persistent = mode0;
+  b->parity = parity0;
   const int rc2 = copy_state(false);
   if (rc == LBM_OK) rc = rc2;
   if (hipStreamSynchronize(b->stream) != hipSuccess && rc == LBM_OK) rc = set_error(LBM_EHIP, "autotune sync");
-  b->parity = parity0;
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   (void)hipFree(snap);
