@@ -40,12 +40,16 @@ TileGrid grid_of(const lbm_ltne_params& p, int w, int h) {
   return g;
 }
 
+// Passes of the busiest CU, which holds ceil(tiles / 256) tiles.
+long long busiest_passes(const TileGrid& g, int nsub) {
+  return static_cast<long long>(ceil_div(g.ntiles, kCus)) * tile_passes(g.w, g.h, nsub);
+}
+
 // The shape with the fewest passes among those that split both axes evenly and
 // whose halo of nsub - 1 nodes fits `slots` slots; among equals the widest
-// rows.  per_cu: passes of the busiest CU, which holds ceil(tiles / 256)
-// tiles; else of all tiles together.  For each width the heights that can be
-// the best are tried: the tallest tiles and the next three that give another
-// count.
+// rows.  per_cu: passes of the busiest CU; else of all tiles together.  For each
+// width the heights that can be the best are tried: the tallest tiles and the
+// next three that give another count.
 TileGrid best_shape(const lbm_ltne_params& p, int nsub, int slots, bool per_cu) {
   // the next smaller even split of n nodes than tiles of size s
   auto next = [](int n, int s) { return ceil_div(n, ceil_div(n, s - 1)); };
@@ -62,8 +66,8 @@ TileGrid best_shape(const lbm_ltne_params& p, int nsub, int slots, bool per_cu) 
       const int he = std::max(4, ceil_div(p.ny, nty));
       if (rows_fit(p, he)) {
         const TileGrid g = grid_of(p, we, he);
-        const long long c = static_cast<long long>(per_cu ? ceil_div(g.ntiles, kCus) : g.ntiles) *
-                            tile_passes(we, he, nsub);
+        const long long c = per_cu ? busiest_passes(g, nsub)
+                                   : static_cast<long long>(g.ntiles) * tile_passes(we, he, nsub);
         if (best.ntiles == 0 || c < least) {
           best = g;
           least = c;
@@ -79,12 +83,18 @@ TileGrid best_shape(const lbm_ltne_params& p, int nsub, int slots, bool per_cu) 
 
 }  // namespace
 
-// Large lattices (2048 tiles and more, eight per CU) take the shape that ran
-// fastest on a layer (us per step, three steps: 4096^2 binary32 48 x 16: 251,
-// 32 x 24: 255, 64 x 11: 255, 28 x 28: 260; 4096 x 2048 binary64 24 x 15: 225,
-// 32 x 10: 232, 20 x 18: 233, 16 x 22: 241; 3072^2 f32sr 48 x 16: 210,
-// 32 x 24: 208, 64 x 11: 216; 3072 x 2048 binary16 54 x 30: 82, 64 x 26: 82,
-// 32 x 52: 84).  On smaller ones a launch takes 4.2 us plus 0.23 us (binary32)
+// Large lattices (2048 tiles and more, eight per CU) take one shape that ran
+// fastest, or within 1% of it, on a layer (us per step, three steps: 4096^2
+// binary32 48 x 16: 251, 32 x 24: 255, 64 x 11: 255, 28 x 28: 260; 4096 x 2048
+// binary64 24 x 15: 225, 32 x 10: 232, 20 x 18: 233, 16 x 22: 241; 3072^2 f32sr
+// 48 x 16: 210, 32 x 24: 208, 64 x 11: 216; 3072 x 2048 binary16 54 x 30: 82,
+// 64 x 26: 82, 32 x 52: 84) -- unless that shape leaves so much of its last
+// tiles empty that it takes over 4/3 times the passes of the best even split.
+// Of 128 large lattices from 24 to 400000 nodes wide, those up to that line ran
+// at 0.90 to 1.19 times the even split's time with the one shape, those past it
+// at 1.00 to 1.64 (400000 x 6 binary64 126 us a step, 89 with the even split;
+// 49 x 40000 f32sr 98, 66; 55 x 40000 binary16 62, 38), and those alone had been
+// slower than single steps or a register window (108, 78, 46).  On smaller ones a launch takes 4.2 us plus 0.23 us (binary32)
 // times the passes of the busiest CU, which holds ceil(tiles / 256) tiles (two
 // steps, checked from 257 x 193 to 1024^2 within 3%): that product is made
 // smallest.
@@ -92,11 +102,13 @@ TileGrid tile_grid(const lbm_ltne_params& p, int nsub) {
   // by steps and precision
   static const int wide[2][4][2] = {{{32, 13}, {64, 14}, {62, 24}, {48, 16}}, {{24, 15}, {48, 16}, {54, 30}, {48, 16}}};
   const int w = wide[nsub - 2][p.precision][0], h = wide[nsub - 2][p.precision][1];
+  const TileGrid even = best_shape(p, nsub, tile_slots(p.precision), true);
   if (p.nx >= w && rows_fit(p, h)) {
     const TileGrid g = grid_of(p, w, h);
-    if (g.ntiles >= 8 * kCus) return g;
+    if (g.ntiles >= 8 * kCus && (even.ntiles == 0 || 3 * busiest_passes(g, nsub) <= 4 * busiest_passes(even, nsub)))
+      return g;
   }
-  return best_shape(p, nsub, tile_slots(p.precision), true);
+  return even;
 }
 
 // A lattice is small if at most 256 tiles, one a CU, cover it with at least
