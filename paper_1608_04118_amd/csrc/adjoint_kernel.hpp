@@ -496,32 +496,35 @@ static_assert(kRows == 1, "the adjoint kernel takes one node (or one part of one
 
 // One node's part of a sweep.  Lm: storage type of the adjoint populations,
 // C: arithmetic type, R: type of the lattice's fields and recorded sums.
-// Bulk: a node not next to a wall, in a lane of its own; slot: the part of the
-// node that this lane takes otherwise (see AdjGrid);
+// bulk: whether it is a node not next to a wall, in a lane of its own; slot:
+// the part of the node that this lane takes otherwise (see AdjGrid).  Bulk:
+// std::true_type or std::false_type where the caller has a body for each, or
+// bool for one body;
 // mu_in(i, x, y, sx, sy, nx): the previous sweep's mu_i at (sx, sy), the node
 // one velocity away from (x, y); wall_grad(ib, gp, gh): adds to the gradients
 // of a wall node; done(iz, mu, gp, gh, m, D0): the results of
 // node iz, called by its lane of slot 0.
-template <typename Lm, typename C, typename R, int Mode, bool Bulk, class Mu, class WallGrad, class Done>
-__device__ __forceinline__ void adjoint_node(const int x, const int y, const int slot, const bool valid,
-                                             const Mu& mu_in, const R* __restrict__ rec,
+template <typename Lm, typename C, typename R, int Mode, class Bulk, class Mu, class WallGrad, class Done>
+__device__ __forceinline__ void adjoint_node(const Bulk bulk, const int x, const int y, const int slot,
+                                             const bool valid, const Mu& mu_in, const R* __restrict__ rec,
                                              const R* __restrict__ phi_field, const R* __restrict__ hv_field,
                                              const R* __restrict__ wseed, const R* __restrict__ init_tf,
                                              const R* __restrict__ init_ts, const StepConsts<C>& k,
                                              const WallGrad& wall_grad, const Done& done) {
+  constexpr bool kBulk = std::is_same<Bulk, std::true_type>::value;
   const int nx = k.nx, ny = k.ny;
   const int iz = y * nx + x;
   // the wall this lane takes (slots 1-3), if any
   const int cx = (!k.px && x == 1) ? 0 : ((!k.px && x == nx - 2) ? nx - 1 : -1);
   const int cy = (!k.py && y == 1) ? 0 : ((!k.py && y == ny - 2) ? ny - 1 : -1);
-  const bool has_wall = !Bulk && Mode != kAdjSeed &&
+  const bool has_wall = !bulk && Mode != kAdjSeed &&
                         ((slot == 1 && cx >= 0) || (slot == 2 && cy >= 0) || (slot == 3 && cx >= 0 && cy >= 0));
   const bool active = valid && (slot == 0 || has_wall);
   const int ax = (slot == 2) ? x : cx, ay = (slot == 1) ? y : cy;  // wall node of slots 1-3
   // own (slot 0) or wall adjoint populations first, so the loads overlap the
   // arithmetic
   Lm lam[19];
-  if (Mode != kAdjSeed && active) gather_lambda<Bulk>(mu_in, slot == 0 ? x : ax, slot == 0 ? y : ay, k, lam);
+  if (Mode != kAdjSeed && active) gather_lambda<kBulk>(mu_in, slot == 0 ? x : ax, slot == 0 ? y : ay, k, lam);
   NodeMacros<C> m;
   C D0 = C(0);
   MacroAdj<C> bar;
@@ -554,7 +557,7 @@ __device__ __forceinline__ void adjoint_node(const int x, const int y, const int
     } else if (active) {
       MomAdj<Lm> L;
       mom_adjoint(lam, L);
-      if (Bulk || slot == 0) {
+      if (kBulk || slot == 0) {
         adj_interior(m, L, bar, k);
       } else {
         const int ib = ay * nx + ax;
@@ -569,7 +572,7 @@ __device__ __forceinline__ void adjoint_node(const int x, const int y, const int
       relax_add(rx, L, k);
     }
   }
-  if (!Bulk) quad_sum(bar, rx);
+  if (!bulk) quad_sum(bar, rx);
   if (!valid || slot != 0) return;
   C nu[5], gpz, ghz;
   adj_backprop(m, bar, nu, gpz, ghz, k);
@@ -651,6 +654,19 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(
     gphi[iz] += gpd;
     ghv[iz] += ghd;
   };
+  auto node = [&](auto bulk, int x, int y, int slot, bool valid) {
+    adjoint_node<Lm, C, R, Mode>(bulk, x, y, slot, valid, mu_in, rec, phi_field, hv_field, wseed, init_tf, init_ts, k,
+                                 wall_grad, done);
+  };
+  // One body for nodes next to a wall and others in binary32, where two in one
+  // kernel take 111 registers (four wavefronts a SIMD) and one takes 87 (five):
+  // a sweep of 512^2 nodes 19.2 us with two, 17.2 with one.  In binary64 both
+  // leave two wavefronts, and the body without wall code is faster: 33.0 us with
+  // two, 35.5 with one.  The f32sr form keeps two: its sweep gained as well (17.9
+  // to 16.1 us), but whole calls measured 0 to 4% longer.
+  constexpr bool one_body = sizeof(Lm) == 4 && sizeof(R) == 4;
+  int x = 1, y = 1, slot = 0;
+  bool valid = true;
   if (b < g.bulk_blocks) {
     const int t = (b & (kXcds - 1)) * g.tm.per_xcd + (b >> 3);
     if (t >= g.tm.ntiles) return;
@@ -658,19 +674,20 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(
     const int xl = (t % g.tm.ntx) * tw + (static_cast<int>(threadIdx.x) & (tw - 1));
     const int yl = (t / g.tm.ntx) * (kBlock >> g.tm.tw_shift) + (static_cast<int>(threadIdx.x) >> g.tm.tw_shift);
     if (xl >= g.bw || yl >= g.bh) return;
-    adjoint_node<Lm, C, R, Mode, true>(g.bx0 + xl, g.by0 + yl, 0, true, mu_in, rec, phi_field, hv_field, wseed, init_tf,
-                                       init_ts, k, wall_grad, done);
+    x = g.bx0 + xl;
+    y = g.by0 + yl;
+    if constexpr (!one_body) node(std::true_type{}, x, y, 0, true);
   } else {
     // four lanes per edge node; every lane of the wavefront stays to the
     // cross-lane sums
     const int e4 = (b - g.bulk_blocks) * kBlock + static_cast<int>(threadIdx.x);
     const int e = e4 >> 2;
-    const bool valid = e < g.nedge;
-    int x = 1, y = 1;
+    slot = e4 & 3;
+    valid = e < g.nedge;
     if (valid) edge_node(e, g, nx, ny, x, y);
-    adjoint_node<Lm, C, R, Mode, false>(x, y, e4 & 3, valid, mu_in, rec, phi_field, hv_field, wseed, init_tf, init_ts,
-                                        k, wall_grad, done);
+    if constexpr (!one_body) node(std::false_type{}, x, y, slot, valid);
   }
+  if constexpr (one_body) node(b < g.bulk_blocks, x, y, slot, valid);
 }
 
 }  // namespace ltne

@@ -140,8 +140,8 @@ __global__ __launch_bounds__((AdjTileForm<Lm>::Block), (AdjTileForm<Lm>::Waves))
       const bool own = x >= x0 && x < x1 && y >= y0 && y < y1;
       if (k.px) x = wrap1(x, nx);
       if (k.py) y = wrap1(y, ny);
-      adjoint_node<Lm, C, R, kAdjStep, decltype(bulk)::value>(
-          x, y, slot, true, mu_in, rec1, phi_field, hv_field, static_cast<const R*>(nullptr),
+      adjoint_node<Lm, C, R, kAdjStep>(
+          bulk, x, y, slot, true, mu_in, rec1, phi_field, hv_field, static_cast<const R*>(nullptr),
           static_cast<const R*>(nullptr), static_cast<const R*>(nullptr), kk,
           [&](int ib, double gp, double gh) {
             if (own) {
@@ -163,8 +163,8 @@ __global__ __launch_bounds__((AdjTileForm<Lm>::Block), (AdjTileForm<Lm>::Waves))
   for_adj_nodes(AdjNodes(interior(0), k), t, Form::Block, k, [&](int x, int y, int slot, auto bulk) {
     const StepConsts<C>& kk = fresh<C>(kp);
     const int s = (y - y0 + 1) * P + (x - x0 + 1), o = (y - y0) * (x1 - x0) + (x - x0);
-    adjoint_node<Lm, C, R, kAdjStep, decltype(bulk)::value>(
-        x, y, slot, true, LdsMu<Lm, N>{mus + s, x, y, P}, rec0, phi_field, hv_field, static_cast<const R*>(nullptr),
+    adjoint_node<Lm, C, R, kAdjStep>(
+        bulk, x, y, slot, true, LdsMu<Lm, N>{mus + s, x, y, P}, rec0, phi_field, hv_field, static_cast<const R*>(nullptr),
         static_cast<const R*>(nullptr), static_cast<const R*>(nullptr), kk,
         [&](int ib, double gp, double gh) {
           gphi[ib] += gp;
