@@ -303,11 +303,14 @@ int lbm_ltne_batch_set_chunks(lbm_ltne_batch_t b, const int32_t *rows);
 int lbm_ltne_batch_get_chunks(lbm_ltne_batch_t b, int32_t *rows);
 /* Autotuner: for each size class (lattices of equal nx) tries tile widths
  * 64/128/256 by timing reps single-step launches, then (FP32 batches whose
- * persistent launch runs pairs of steps) chunk heights 8..32 by timing 6 reps
+ * persistent launch runs pairs of steps) chunk heights 8..32 by timing 2 reps
  * steps of that launch, then the launch mode (launches of several steps, or
- * one persistent launch; skipped when the device has no resident
- * grid for it, not taken where one of its barriers times out) by timing 6 reps steps of each, every trial from a snapshot
- * of the state (restored afterwards), and keeps the fastest of each;
+ * one persistent launch; skipped when the device has no resident grid for it,
+ * not taken where one of its barriers times out) by timing about 2 reps steps
+ * of each, every trial from a snapshot of the state (restored afterwards), and
+ * keeps the fastest of each.  Mode 0 takes the tile widths only where a single
+ * step is left over, and the chunk heights nowhere: the tiles of its launches
+ * of several steps follow from the lattices' sizes.
  * ms_per_step (may be NULL) receives the time per step of the chosen
  * configuration on the path the batch runs (launches of several steps where they
  * apply).  Allocates a snapshot of the populations for the call. */

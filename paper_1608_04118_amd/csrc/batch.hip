@@ -837,23 +837,25 @@ int lbm_ltne_batch_autotune(lbm_ltne_batch_t b, int32_t reps, double* ms_per_ste
     }
     for (int i : kv.second) b->shift[i] = best_shift;
   }
-  // Time per step over 6 reps steps of launch mode m, from the snapshot (whole
-  // launches of two and of three steps).
+  // Time per step of launch mode m, from the snapshot, over about 2 reps steps:
+  // whole launches of two and of three steps, pairs in the persistent launch
+  // (the slower one, whose trials are most of the call).
   const int mode0 = b->persistent;
   auto trial2 = [&](int m, float* ms) -> int {
     b->persistent = m;
     int r = copy_state(false);
     if (r != LBM_OK) return r;
     b->parity = parity0;
-    r = launch_batch(b, 6, 0, true);  // warm-up
+    const int steps = m ? 2 * reps : 6 * ((reps + 2) / 3);
+    r = launch_batch(b, m ? 2 : 6, 0, true);  // warm-up
     if (r != LBM_OK) return r;
     HIP_TRY(hipEventRecord(e0, b->stream));
-    r = launch_batch(b, 6 * reps, 0, true);
+    r = launch_batch(b, steps, 0, true);
     if (r != LBM_OK) return r;
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
-    *ms /= static_cast<float>(6 * reps);
+    *ms /= static_cast<float>(steps);
     b->parity = parity0;
     return settle(ms);
   };
