@@ -201,8 +201,10 @@ int64_t lbm_ltne_steps_done(lbm_ltne_t h);
 /* Copies the macroscopic fields of the current time to host arrays of nx*ny
  * doubles: rho (Eq. 18), u (Eq. 20), T_f, T_s (Eqs. 43-44); wall nodes report
  * their prescribed values.  Any pointer may be NULL.  Synchronizes.
- * The handle keeps up to 24 MB of pinned staging memory from the first call
- * on; large fields are moved by up to 8 threads that end with the call. */
+ * Fields of more than 512 KB go through up to 24 MB of pinned memory, which
+ * the handles of the process share (one piece for each thread that reads at
+ * the same time, at most 8 kept) until the last handle is destroyed; large
+ * fields are moved by up to 8 threads that end with the call. */
 int lbm_ltne_macros(lbm_ltne_t h, double *rho, double *ux, double *uy, double *Tf, double *Ts);
 
 /* Mean Nusselt numbers of the fluid and solid phase over wall p->nu_wall:

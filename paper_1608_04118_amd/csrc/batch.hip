@@ -242,7 +242,7 @@ struct lbm_ltne_batch {
   int grid2 = 0;      // most workgroups of the persistent two-step launch (FP32)
   size_t consts_bytes = 0, desc_bytes = 0;
   long long nodes = 0;
-  Staging staging;  // of lbm_ltne_batch_macros
+  StagingHold staging;  // of lbm_ltne_batch_macros
   bool barriers = false;  // a persistent launch was queued, so ctl may hold a timeout
   unsigned spin_limit = kSpinLimit;  // polls of a barrier wait of the persistent launch
 
@@ -912,7 +912,7 @@ int lbm_ltne_batch_macros(lbm_ltne_batch_t b, int32_t i, double* rho, double* ux
   const long long n = b->n_of(i);
   const size_t cb = compute_bytes(b->precision);
   double* const outs[5] = {rho, ux, uy, Tf, Ts};
-  HIP_TRY(read_fields(b->staging, b->device, b->stream, b->base + b->off_mac[i], static_cast<int>(cb), n, outs));
+  HIP_TRY(read_fields(b->device, b->stream, b->base + b->off_mac[i], static_cast<int>(cb), n, outs));
   return LBM_OK;
 }
 

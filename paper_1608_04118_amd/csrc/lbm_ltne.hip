@@ -36,7 +36,7 @@ struct lbm_ltne {
   std::vector<double> tf0, ts0;  // initial temperature fields (if given), for the adjoint
   TileGrid tiles[2] = {};  // tiles of the launches of two and three steps
   SmallTiles small{};      // tiles and steps of a small lattice's launches
-  Staging staging;         // of lbm_ltne_macros
+  StagingHold staging;     // of lbm_ltne_macros
 
   void* pop(int i) const { return base + lay.off_pop[i]; }
   void* mac(int i) const { return base + lay.off_mac[i]; }
@@ -428,7 +428,7 @@ int lbm_ltne_macros(lbm_ltne_t h, double* rho, double* ux, double* uy, double* T
   const long long n = h->n();
   const size_t cb = compute_bytes(h->p.precision);
   double* const outs[5] = {rho, ux, uy, Tf, Ts};
-  HIP_TRY(read_fields(h->staging, h->device, h->stream, h->mac(h->mcur), static_cast<int>(cb), n, outs));
+  HIP_TRY(read_fields(h->device, h->stream, h->mac(h->mcur), static_cast<int>(cb), n, outs));
   return check_diverged(h, LBM_OK);
 }
 

@@ -18,8 +18,11 @@
 #include <cstring>
 #include <exception>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <thread>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 namespace ltne {
@@ -40,6 +43,56 @@ constexpr int kMaxThreads = 8;
 // freeing it takes 50 us, and a pageable copy reads 160 KB in 24 us against 23,
 // 500 KB in 50 against 43.
 constexpr size_t kPageable = 512 << 10;
+
+// Pinned chunks in flight of one readback, and their events: 24 MB at most in
+// binary64, 12 MB in binary32, no more than the fields that it has read need.
+struct Staging {
+  static constexpr int kSlots = 12;
+  const int device;
+  char* buf = nullptr;
+  size_t bytes = 0;
+  hipEvent_t ev[kSlots] = {};
+  int nev = 0;
+  explicit Staging(int d) : device(d) {}
+  Staging(const Staging&) = delete;
+  Staging& operator=(const Staging&) = delete;
+  ~Staging() {
+    for (int i = 0; i < nev; ++i) (void)hipEventDestroy(ev[i]);
+    if (buf) (void)hipHostFree(buf);
+  }
+};
+
+// As many as threads that read at the same time are likely to be.
+constexpr int kKeptStagings = 8;
+
+// The process's pieces that no readback uses, and the handles alive.  Nothing
+// is left to do when the process ends (a handle never closed leaves its memory
+// to the system, as its device memory).
+struct StagingPool {
+  std::mutex m;
+  Staging* kept[kKeptStagings] = {};
+  int nkept = 0;
+  long long handles = 0;
+} g_pool;
+static_assert(std::is_trivially_destructible<StagingPool>::value, "used by handles closed at the end of the process");
+
+// A piece on the device, of `least` bytes where one is kept, else any or none.
+std::unique_ptr<Staging> take_staging(int device, size_t least) {
+  std::lock_guard<std::mutex> lock(g_pool.m);
+  int at = -1;
+  for (int i = 0; i < g_pool.nkept; ++i)
+    if (g_pool.kept[i]->device == device && (at < 0 || g_pool.kept[at]->bytes < least)) at = i;
+  if (at < 0) return nullptr;
+  std::unique_ptr<Staging> s(g_pool.kept[at]);
+  g_pool.kept[at] = g_pool.kept[--g_pool.nkept];
+  return s;
+}
+
+// Back after a readback (no copy into it is in flight).
+void keep_staging(std::unique_ptr<Staging> s) {
+  std::lock_guard<std::mutex> lock(g_pool.m);
+  if (s && s->bytes > 0 && g_pool.nkept < kKeptStagings) g_pool.kept[g_pool.nkept++] = s.release();
+}
 
 struct Run {  // `count` values from value `at` of the fields on
   long long at, count;
@@ -99,12 +152,12 @@ void cut(std::vector<Run>& runs, long long n, double* const outs[5]) {
 }
 
 // Staging memory and events of `nslots` chunks in flight.
-hipError_t reserve(Staging& st, int device, size_t bytes, int nslots) {
+hipError_t reserve(Staging& st, size_t bytes, int nslots) {
   const int nev = nslots > 1 ? nslots : 0;
   if (st.bytes >= bytes && st.nev >= nev) return hipSuccess;
   int before = 0;
   hipError_t e = hipGetDevice(&before);
-  if (e == hipSuccess && before != device) e = hipSetDevice(device);  // the events' device
+  if (e == hipSuccess && before != st.device) e = hipSetDevice(st.device);  // the events' device
   // an allocation leaves a stream capture elsewhere in the process alone
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   if (e == hipSuccess) e = hipThreadExchangeStreamCaptureMode(&mode);
@@ -125,7 +178,7 @@ hipError_t reserve(Staging& st, int device, size_t bytes, int nslots) {
     if (e == hipSuccess) ++st.nev;
   }
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (before != device) (void)hipSetDevice(before);
+  if (before != st.device) (void)hipSetDevice(before);
   return e;
 }
 
@@ -159,15 +212,26 @@ hipError_t read_pageable(hipStream_t stream, const char* src, int elem, long lon
 
 }  // namespace
 
-void Staging::release() {
-  for (int i = 0; i < nev; ++i) (void)hipEventDestroy(ev[i]);
-  nev = 0;
-  if (buf) (void)hipHostFree(buf);
-  buf = nullptr;
-  bytes = 0;
+StagingHold::StagingHold() {
+  std::lock_guard<std::mutex> lock(g_pool.m);
+  ++g_pool.handles;
 }
 
-hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* src_, int elem, long long n,
+StagingHold::~StagingHold() {
+  Staging* last[kKeptStagings];
+  int n = 0;
+  {
+    std::lock_guard<std::mutex> lock(g_pool.m);
+    if (--g_pool.handles == 0) {
+      n = g_pool.nkept;
+      std::copy(g_pool.kept, g_pool.kept + n, last);
+      g_pool.nkept = 0;
+    }
+  }
+  for (int i = 0; i < n; ++i) delete last[i];
+}
+
+hipError_t read_fields(int device, hipStream_t stream, const void* src_, int elem, long long n,
                        double* const outs[5]) {
   const char* const src = static_cast<const char*>(src_);
   if (overlapping(n, outs)) return read_pageable(stream, src, elem, n, outs);
@@ -183,7 +247,9 @@ hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* 
   if (nruns == 0) return hipSuccess;
   const int nslots = std::min(nruns, Staging::kSlots);
   const size_t slot = static_cast<size_t>(nruns == 1 ? runs[0].count : kChunk) * elem;
-  if (nruns == 1 && slot <= kPageable && st.bytes < slot) {
+  std::unique_ptr<Staging> held = take_staging(device, slot * nslots);
+  if (nruns == 1 && slot <= kPageable && (!held || held->bytes < slot)) {
+    keep_staging(std::move(held));
     std::unique_ptr<char[]> tmp(new (std::nothrow) char[slot]);
     if (!tmp) return hipErrorOutOfMemory;
     hipError_t e = hipMemcpyAsync(tmp.get(), src + runs[0].at * elem, slot, hipMemcpyDeviceToHost, stream);
@@ -191,10 +257,13 @@ hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* 
     if (e == hipSuccess) deliver(tmp.get(), runs[0], elem, n, outs, true);
     return e;
   }
-  if (reserve(st, device, slot * nslots, nslots) != hipSuccess) {
+  if (!held) held.reset(new (std::nothrow) Staging(device));
+  if (!held || reserve(*held, slot * nslots, nslots) != hipSuccess) {
     (void)hipGetLastError();
+    held.reset();
     return read_pageable(stream, src, elem, n, outs);
   }
+  Staging& st = *held;
   auto slot_of = [&](int c) { return st.buf + (c % nslots) * slot; };
   auto send = [&](int c) {
     hipError_t e = hipMemcpyAsync(slot_of(c), src + runs[c].at * elem, runs[c].count * elem, hipMemcpyDeviceToHost,
@@ -204,7 +273,9 @@ hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* 
   if (nruns == 1) {
     hipError_t e = send(0);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e == hipSuccess) deliver(slot_of(0), runs[0], elem, n, outs, true);
+    if (e != hipSuccess) return e;
+    deliver(slot_of(0), runs[0], elem, n, outs, true);
+    keep_staging(std::move(held));
     return e;
   }
 
@@ -256,7 +327,10 @@ hipError_t read_fields(Staging& st, int device, hipStream_t stream, const void* 
   }
   if (e != hipSuccess) arrived.store(-1, std::memory_order_release);
   for (std::thread& t : threads) t.join();
-  if (e != hipSuccess) (void)hipStreamSynchronize(stream);  // no copy into the staging memory is left
+  if (e != hipSuccess)
+    (void)hipStreamSynchronize(stream);  // no copy into the staging memory is left
+  else
+    keep_staging(std::move(held));
   return e;
 }
 
