@@ -197,9 +197,9 @@ __global__ __launch_bounds__(kPersistBlock) void batch2p_kernel(
       const CavityDesc<float>& d = cav[c];
       const int local = w - d.wave_begin;
       const int nstrips = (k.nx + step2_out(k.px) - 1) / step2_out(k.px);
-      step2_wave<F, float>(at_offset<const float>(base, d.pop[parity]), at_offset<float>(base, d.pop[parity ^ 1]),
-                    at_offset<const float>(base, d.phi), at_offset<const float>(base, d.hv), nullptr, k,
-                    kts[wl], local % nstrips, local / nstrips, d.rows2, step0 + 2u * static_cast<uint32_t>(s));
+      step2_wave<F>(at_offset<const float>(base, d.pop[parity]), at_offset<float>(base, d.pop[parity ^ 1]),
+                    at_offset<const float>(base, d.phi), at_offset<const float>(base, d.hv), k, kts[wl],
+                    local % nstrips, local / nstrips, d.rows2, step0 + 2u * static_cast<uint32_t>(s));
       __builtin_amdgcn_wave_barrier();
     }
     if (s + 1 < npairs && !grid_barrier(ctl, gridDim.x, gen, spin_limit)) return;

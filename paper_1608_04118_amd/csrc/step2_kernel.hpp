@@ -45,28 +45,22 @@ __host__ __device__ constexpr int step2_waves(int nx, int ny, int periodic_x, in
 // resource per lattice row (its 19 population rows), the population's offset
 // in the scalar offset operand and the lane's column in the vector offset,
 // so no vector instruction is spent forming 64-bit addresses.
-template <typename S>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const S* row, long long rs) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<S*>(row), static_cast<short>(0),
-                                           static_cast<int>(rs * static_cast<long long>(sizeof(S))), 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const float* row, long long rs) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(row), static_cast<short>(0),
+                                           static_cast<int>(rs * static_cast<long long>(sizeof(float))), 0x00020000);
 }
 
 // One element through a buffer resource.
-template <typename S>
-__device__ __forceinline__ S buf_load(__amdgpu_buffer_rsrc_t r, int vo, int so) {
-  static_assert(sizeof(S) == 4, "binary32 storage");
-  return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, int vo, int so) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
 }
-template <typename S>
-__device__ __forceinline__ void buf_store(S v, __amdgpu_buffer_rsrc_t r, int vo, int so) {
-  static_assert(sizeof(S) == 4, "binary32 storage");
+__device__ __forceinline__ void buf_store(float v, __amdgpu_buffer_rsrc_t r, int vo, int so) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, vo, so, 0);
 }
 
-template <typename S>
 struct BufPull {
-  const S* __restrict__ src;
-  __device__ __forceinline__ void operator()(int xc, int yc, const StepConsts<S>& k, S (&v)[kPlanes]) const {
+  const float* __restrict__ src;
+  __device__ __forceinline__ void operator()(int xc, int yc, const StepConsts<float>& k, float (&v)[kPlanes]) const {
     const int nx = k.nx, ny = k.ny;
     const int yu = __builtin_amdgcn_readfirstlane(yc);
     int xm = xc - 1, xp = xc + 1, ym = yu - 1, yp = yu + 1;
@@ -81,10 +75,10 @@ struct BufPull {
     const __amdgpu_buffer_rsrc_t r0 = row_rsrc(src + yu * k.rs, k.rs);
     const __amdgpu_buffer_rsrc_t rm = row_rsrc(src + ym * k.rs, k.rs);
     const __amdgpu_buffer_rsrc_t rp = row_rsrc(src + yp * k.rs, k.rs);
-    constexpr int E = sizeof(S);
+    constexpr int E = sizeof(float);
     const int Q = static_cast<int>(k.qs) * E;
     const int oc = xc * E, om = xm * E, op = xp * E;
-    auto ld = [&](__amdgpu_buffer_rsrc_t r, int vo, int q) { return buf_load<S>(r, vo, q * Q); };
+    auto ld = [&](__amdgpu_buffer_rsrc_t r, int vo, int q) { return buf_load(r, vo, q * Q); };
     v[0] = ld(r0, oc, 0);
     v[1] = ld(r0, om, 1);
     v[2] = ld(rm, oc, 2);
@@ -109,63 +103,60 @@ struct BufPull {
 
 // One field value (porosity or H_v) of node (xc, yc) through a buffer
 // resource over the field's row, so a wavefront's loads are all of one kind.
-template <typename S>
-__device__ __forceinline__ S buf_field(const S* __restrict__ f, int xc, int yc, int nx) {
+__device__ __forceinline__ float buf_field(const float* __restrict__ f, int xc, int yc, int nx) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<S*>(f + static_cast<long long>(__builtin_amdgcn_readfirstlane(yc)) * nx), static_cast<short>(0),
-      nx * static_cast<int>(sizeof(S)), 0x00020000);
-  return buf_load<S>(r, xc * static_cast<int>(sizeof(S)), 0);
+      const_cast<float*>(f + static_cast<long long>(__builtin_amdgcn_readfirstlane(yc)) * nx), static_cast<short>(0),
+      nx * static_cast<int>(sizeof(float)), 0x00020000);
+  return buf_load(r, xc * static_cast<int>(sizeof(float)), 0);
 }
 
-template <int F, typename S>
-__device__ __forceinline__ CenterFields<S> buf_center(const S* __restrict__ phi_field, const S* __restrict__ hv_field,
-                                                      int xc, int yc, const StepConsts<S>& k) {
+template <int F>
+__device__ __forceinline__ CenterFields<float> buf_center(const float* __restrict__ phi_field,
+                                                          const float* __restrict__ hv_field, int xc, int yc,
+                                                          const StepConsts<float>& k) {
   return {(F & kPhiField) ? buf_field(phi_field, xc, yc, k.nx) : k.phi_u,
           (F & kHvField) ? buf_field(hv_field, xc, yc, k.nx) : k.hv_u};
 }
 
-template <typename S>
 struct BufPut {
-  S* __restrict__ dst;
+  float* __restrict__ dst;
   __amdgpu_buffer_rsrc_t r;
   int vo = 0, Q = 0;
-  __device__ __forceinline__ void begin(int x, int y, const StepConsts<S>& k) {
+  __device__ __forceinline__ void begin(int x, int y, const StepConsts<float>& k) {
     r = row_rsrc(dst + static_cast<long long>(__builtin_amdgcn_readfirstlane(y)) * k.rs, k.rs);
-    vo = x * static_cast<int>(sizeof(S));
-    Q = static_cast<int>(k.qs) * static_cast<int>(sizeof(S));
+    vo = x * static_cast<int>(sizeof(float));
+    Q = static_cast<int>(k.qs) * static_cast<int>(sizeof(float));
   }
-  __device__ __forceinline__ void st(int i, S v) { buf_store(v, r, vo, i * Q); }
+  __device__ __forceinline__ void st(int i, float v) { buf_store(v, r, vo, i * Q); }
   template <typename VA, typename VB>
   __device__ __forceinline__ void pair(int i, VA va, VA, int j, VB vb, VB, uint32_t w, half2_t&) {
-    st(i, to_storage<S>(va, w << 16));
-    st(j, to_storage<S>(vb, w));
+    st(i, to_storage<float>(va, w << 16));
+    st(j, to_storage<float>(vb, w));
   }
   template <typename V>
-  __device__ __forceinline__ void single(int i, V v, V, uint32_t w) { st(i, to_storage<S>(v, w)); }
+  __device__ __forceinline__ void single(int i, V v, V, uint32_t w) { st(i, to_storage<float>(v, w)); }
 };
 
 // Put into registers: the 19 post-collision populations of one node, rounded
 // to the storage type exactly as a store to memory would round them (the
 // binary64 temperature values of the FP32 form stochastically, with the
 // same random words), so the intermediate time level equals a single step's.
-template <typename C>
 struct RegPut {
-  C* v;
-  __device__ __forceinline__ void begin(int, int, const StepConsts<C>&) {}
+  float* v;
+  __device__ __forceinline__ void begin(int, int, const StepConsts<float>&) {}
   template <typename VA, typename VB>
   __device__ __forceinline__ void pair(int i, VA va, VA, int j, VB vb, VB, uint32_t w, half2_t&) {
-    v[i] = to_storage<C>(va, w << 16);
-    v[j] = to_storage<C>(vb, w);
+    v[i] = to_storage<float>(va, w << 16);
+    v[j] = to_storage<float>(vb, w);
   }
   template <typename V>
-  __device__ __forceinline__ void single(int i, V val, V, uint32_t r) { v[i] = to_storage<C>(val, r); }
+  __device__ __forceinline__ void single(int i, V val, V, uint32_t r) { v[i] = to_storage<float>(val, r); }
 };
 
 // Pull from registers: populations already gathered for the node.
-template <typename C>
 struct RegPull {
-  const C* g;
-  __device__ __forceinline__ void operator()(int, int, const StepConsts<C>&, C (&v)[kPlanes]) const {
+  const float* g;
+  __device__ __forceinline__ void operator()(int, int, const StepConsts<float>&, float (&v)[kPlanes]) const {
 #pragma unroll
     for (int i = 0; i < kPlanes; ++i) v[i] = g[i];
   }
@@ -177,8 +168,8 @@ struct RegPull {
 // at the end of the row, and that copy waits for every memory access issued
 // before it, stores included.  Uniform fields (not loaded) are left as they
 // are, so that what derives from them stays hoisted out of the row loop.
-template <int F, typename S>
-__device__ __forceinline__ CenterFields<S> detach(CenterFields<S> f) {
+template <int F>
+__device__ __forceinline__ CenterFields<float> detach(CenterFields<float> f) {
   if constexpr ((F & kPhiField) != 0) asm volatile("" : "+v"(f.phi));
   if constexpr ((F & kHvField) != 0) asm volatile("" : "+v"(f.hv));
   return f;
@@ -186,27 +177,23 @@ __device__ __forceinline__ CenterFields<S> detach(CenterFields<S> f) {
 
 // The work of one lane of a strip and chunk: its columns, the chunk's rows,
 // and the three parts of the update (fetch, intermediate level, output).
-template <typename S, int F>
+template <int F>
 struct Step2Lane {
-  const S* __restrict__ src;
-  S* __restrict__ dst;
-  const S* __restrict__ phi_field;
-  const S* __restrict__ hv_field;
-  S* __restrict__ mac;  // macros of the second step (F & kMacros)
-  const StepConsts<S>& k;
+  const float* __restrict__ src;
+  float* __restrict__ dst;
+  const float* __restrict__ phi_field;
+  const float* __restrict__ hv_field;
+  const StepConsts<float>& k;
   const ThermalK<double>& kt;
   uint32_t step;
   int lane, col, xo, dx, y_lo, y_hi;
   bool colok, outlane;
-  // the intermediate level writes no macros
-  static constexpr int FA = F & ~kMacros;
 
-  __device__ __forceinline__ Step2Lane(const S* __restrict__ src_, S* __restrict__ dst_,
-                                       const S* __restrict__ phi_, const S* __restrict__ hv_,
-                                       S* __restrict__ mac_, const StepConsts<S>& k_,
-                                       const ThermalK<double>& kt_, const int strip, const int chunk, const int rows,
-                                       const uint32_t step_)
-      : src(src_), dst(dst_), phi_field(phi_), hv_field(hv_), mac(mac_), k(k_), kt(kt_), step(step_) {
+  __device__ __forceinline__ Step2Lane(const float* __restrict__ src_, float* __restrict__ dst_,
+                                       const float* __restrict__ phi_, const float* __restrict__ hv_,
+                                       const StepConsts<float>& k_, const ThermalK<double>& kt_, const int strip,
+                                       const int chunk, const int rows, const uint32_t step_)
+      : src(src_), dst(dst_), phi_field(phi_), hv_field(hv_), k(k_), kt(kt_), step(step_) {
     lane = static_cast<int>(threadIdx.x) & 63;
     const int nx = k.nx, ny = k.ny;
     const int halo = step2_halo(k.px), out = step2_out(k.px);
@@ -244,14 +231,14 @@ struct Step2Lane {
   // the pulls of node (col, r) at time t (a wall node pulls those of its
   // inward neighbour) and the porosity and H_v there, issued ahead of their
   // use so the loads overlap arithmetic
-  __device__ __forceinline__ void fetch(int r, S (&v)[kPlanes], CenterFields<S>& cf) const {
+  __device__ __forceinline__ void fetch(int r, float (&v)[kPlanes], CenterFields<float>& cf) const {
     bool ok;
     r = row_of(r, ok);
     if (ok) {
       const int nx = k.nx, ny = k.ny;
       const int xc = (!k.px && col == 0) ? 1 : ((!k.px && col == nx - 1) ? nx - 2 : col);
       const int yc = (!k.py && r == 0) ? 1 : ((!k.py && r == ny - 1) ? ny - 2 : r);
-      const BufPull<S> gpull{src};
+      const BufPull gpull{src};
       gpull(xc, yc, k, v);
       cf = buf_center<F>(phi_field, hv_field, xc, yc, k);
     }
@@ -259,33 +246,33 @@ struct Step2Lane {
 
   // node (col, r) at time t + 1 from its fetched pulls and fields into w;
   // zeros where there is no node
-  __device__ __forceinline__ void advance(int r, const S (&v)[kPlanes], const CenterFields<S>& cf,
-                                          S (&w)[kPlanes]) const {
+  __device__ __forceinline__ void advance(int r, const float (&v)[kPlanes], const CenterFields<float>& cf,
+                                          float (&w)[kPlanes]) const {
     bool ok;
     r = row_of(r, ok);
     if (ok) {
-      const RegPull<S> rp{v};
-      RegPut<S> put{w};
-      node_update_with<S, S, FA>(col, r, rp, put, phi_field, hv_field, nullptr, nullptr, nullptr, k, step,
+      const RegPull rp{v};
+      RegPut put{w};
+      node_update_with<float, float, F>(col, r, rp, put, phi_field, hv_field, nullptr, nullptr, nullptr, k, step,
                                         nullptr, kt, &cf);
     } else {
 #pragma unroll
-      for (int i = 0; i < kPlanes; ++i) w[i] = S(0);
+      for (int i = 0; i < kPlanes; ++i) w[i] = float(0);
     }
   }
 
   // node (xo, y) at time t + 2 from its gathered pulls g (time t + 1) and the
   // fields fy of its pulled node, stored; then the wall row it feeds (one
   // call site)
-  __device__ __forceinline__ void output(int y, const S (&g)[kPlanes], const CenterFields<S>& fy) const {
-    const RegPull<S> rpull{g};
-    BufPut<S> put{dst};
+  __device__ __forceinline__ void output(int y, const float (&g)[kPlanes], const CenterFields<float>& fy) const {
+    const RegPull rpull{g};
+    BufPut put{dst};
     const int ny = k.ny;
     const int nrep = (!k.py && (y == 1 || y == ny - 2)) ? 2 : 1;
 #pragma nounroll
     for (int rep = 0; rep < nrep; ++rep) {
       const int yy = rep == 0 ? y : (y == 1 ? 0 : ny - 1);
-      node_update_with<S, S, F>(xo, yy, rpull, put, phi_field, hv_field, mac, nullptr, nullptr, k,
+      node_update_with<float, float, F>(xo, yy, rpull, put, phi_field, hv_field, nullptr, nullptr, nullptr, k,
                                         step + 1u, nullptr, kt, &fy);
     }
   }
@@ -297,21 +284,20 @@ struct Step2Lane {
 //   2. gathers the pulls of its node at row y from the window, the column
 //      offsets by cross-lane permutes;
 //   3. updates the node at row y to time t + 2 and stores it.
-// kt: the lattice's temperature constants, a copy in LDS (see the kernels).
-// mac: the macros of the second step (F & kMacros), else unused.
-template <int F, typename S>
-__device__ __forceinline__ void step2_wave(const S* __restrict__ src, S* __restrict__ dst,
-                                           const S* __restrict__ phi_field, const S* __restrict__ hv_field,
-                                           S* __restrict__ mac, const StepConsts<S>& k,
-                                           const ThermalK<double>& kt, const int strip, const int chunk,
-                                           const int rows, const uint32_t step) {
-  const Step2Lane<S, F> L(src, dst, phi_field, hv_field, mac, k, kt, strip, chunk, rows, step);
+// It writes no macros.  kt: the lattice's temperature constants, a copy in LDS
+// (see the kernel).
+template <int F>
+__device__ __forceinline__ void step2_wave(const float* __restrict__ src, float* __restrict__ dst,
+                                           const float* __restrict__ phi_field, const float* __restrict__ hv_field,
+                                           const StepConsts<float>& k, const ThermalK<double>& kt, const int strip,
+                                           const int chunk, const int rows, const uint32_t step) {
+  const Step2Lane<F> L(src, dst, phi_field, hv_field, k, kt, strip, chunk, rows, step);
   const int y_lo = L.y_lo, y_hi = L.y_hi, lane = L.lane, dx = L.dx;
   if (y_lo >= y_hi) return;
 
-  S wa[kPlanes], wb[kPlanes], wc[kPlanes];  // time t + 1 at rows y - 1, y, y + 1
-  S pa[kPlanes], pb[kPlanes];               // fetched pulls of two rows
-  CenterFields<S> fa{}, fb{};               // and the fields fetched with them
+  float wa[kPlanes], wb[kPlanes], wc[kPlanes];  // time t + 1 at rows y - 1, y, y + 1
+  float pa[kPlanes], pb[kPlanes];               // fetched pulls of two rows
+  CenterFields<float> fa{}, fb{};               // and the fields fetched with them
   L.fetch(y_lo - 1, pa, fa);
   L.fetch(y_lo, pb, fb);
   L.advance(y_lo - 1, pa, fa, wa);
@@ -319,19 +305,19 @@ __device__ __forceinline__ void step2_wave(const S* __restrict__ src, S* __restr
   L.advance(y_lo, pb, fb, wb);
   // fields of node (col, y), the pulled node of the output update at row y
   // (on an output lane col = xo, and a wall row pulls from row y as well)
-  CenterFields<S> fy = detach<F>(fb);
+  CenterFields<float> fy = detach<F>(fb);
 #pragma nounroll
   for (int y = y_lo; y < y_hi; ++y) {
     L.advance(y + 1, pa, fa, wc);
-    const CenterFields<S> fn = detach<F>(fa);
+    const CenterFields<float> fn = detach<F>(fa);
     if (y + 1 < y_hi) L.fetch(y + 2, pa, fa);
     // pulls of node (xo + dx, y) at time t + 1: population i from column
     // xo + dx - e_ix (lane offset) and row y - e_iy (window row)
-    S g[kPlanes];
+    float g[kPlanes];
 #pragma unroll
     for (int i = 0; i < kPlanes; ++i) {
       const int q = i < 9 ? i : (i < 14 ? i - 9 : i - 14);
-      const S v = vel_y(q) == 1 ? wa[i] : (vel_y(q) == -1 ? wc[i] : wb[i]);
+      const float v = vel_y(q) == 1 ? wa[i] : (vel_y(q) == -1 ? wc[i] : wb[i]);
       const int sl = (lane + dx - vel_x(q)) & 63;
       g[i] = __shfl(v, sl, 64);
     }
