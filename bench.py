@@ -410,9 +410,9 @@ def clock_probe(forms=("f32", "f16s", "f64"), samples: int = 6, interval_s: floa
 
 
 def persist_probe(mode: int, steps: int = 200):
-    """16 cavities of 64^2 (FP32; the single-step batch kernel) stepped in one
-    call in the given launch mode (0: a launch per step, 1: persistent), for
-    counter runs comparing the modes."""
+    """16 cavities of 64^2 (FP32) stepped in one call in the given launch mode
+    (0: launches of three steps, 1: persistent, single steps between barriers),
+    for counter runs comparing the modes."""
     import torch
     from paper_1608_04118_amd import binding as B
     from paper_1608_04118_amd import inputs as I

@@ -285,7 +285,7 @@ int lbm_ltne_batch_macros(lbm_ltne_batch_t b, int32_t i, double *rho, double *ux
                           double *Tf, double *Ts);
 /* Mean Nusselt numbers of lattice i (definition of lbm_ltne_nusselt). */
 int lbm_ltne_batch_nusselt(lbm_ltne_batch_t b, int32_t i, double *Nu_f, double *Nu_s);
-/* 0: one launch per step (default), 1: persistent cooperative launch (LBM_EUNSUPPORTED if the
+/* 0: launches of several steps (default), 1: persistent cooperative launch (LBM_EUNSUPPORTED if the
  * device cannot keep a grid resident). */
 int lbm_ltne_batch_set_mode(lbm_ltne_batch_t b, int32_t persistent);
 /* Polls after which a barrier wait of the persistent launch gives up (0: the
@@ -293,10 +293,11 @@ int lbm_ltne_batch_set_mode(lbm_ltne_batch_t b, int32_t persistent);
  * lost, which the next synchronizing call reports as LBM_EHIP; the autotuner
  * restores the state and does without the mode. */
 int lbm_ltne_batch_set_spin_limit(lbm_ltne_batch_t b, uint32_t polls);
-/* Total nodes, tiles, persistent grid size (workgroups) and current mode. */
+/* Total nodes, tiles of a single step, workgroups that a persistent launch has, and current mode. */
 int lbm_ltne_batch_info(lbm_ltne_batch_t b, int64_t *nodes, int32_t *tiles, int32_t *grid,
                         int32_t *persistent);
-/* Tile width of each lattice as log2 (6, 7, 8 = 64, 128, 256 nodes wide; 0 = default). */
+/* Tile width of each lattice as log2 (6, 7, 8 = 64, 128, 256 nodes wide; 0 = default), in the
+ * launches of a single step and the persistent launch of single steps. */
 int lbm_ltne_batch_set_tiles(lbm_ltne_batch_t b, const int32_t *tile_shift);
 int lbm_ltne_batch_get_tiles(lbm_ltne_batch_t b, int32_t *tile_shift);
 /* Chunk height (rows) of each lattice's wavefronts in the persistent launch

@@ -1,14 +1,13 @@
 // Batched execution: many independent lattices of uneven size and
-// parameters advanced together, either by one launch per step over the
-// combined tile list (the default), or by one persistent cooperative launch
-// that loops over the time steps with a grid-wide barrier between steps.
-// The ordinary launches advance two or three steps over tiles held in LDS
-// (tile_kernel.hpp).
-// On MI355X the barrier's device-scope release and acquire (L2 write-back
-// and invalidation on every XCD, once per resident workgroup) cost more than
-// a kernel launch per step, so the per-step form is the default.  Every lattice keeps
-// its own populations, parameter block and macro buffer; the per-node update
-// is the same node_update as the single-lattice kernel.
+// parameters advanced together, either by launches of two or three steps over
+// all lattices' tiles, held in LDS (tile_kernel.hpp; the default, with a launch
+// of its own for a step left over), or by one persistent cooperative launch
+// that loops over the time steps with a grid-wide barrier between steps or
+// pairs of steps.  On MI355X the barrier's device-scope release and acquire (L2
+// write-back and invalidation on every XCD, once per resident workgroup) cost
+// more than a kernel launch.  Every lattice keeps its own populations,
+// parameter block and macro buffer; the per-node update is the same
+// node_update as the single-lattice kernel.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -237,7 +236,7 @@ struct lbm_ltne_batch {
   int fields = 0;     // kPhiField / kHvField if any lattice has that field
   int parity = 0;     // buffer holding the current state
   int64_t steps = 0;
-  int persistent = 0; // 1: cooperative persistent launch, 0: one launch per step (default, faster)
+  int persistent = 0; // 1: cooperative persistent launch, 0: launches of several steps (default, faster)
   int grid = 0;       // most workgroups of the persistent launch
   int grid2 = 0;      // most workgroups of the persistent two-step launch (FP32)
   size_t consts_bytes = 0, desc_bytes = 0;

@@ -13,8 +13,8 @@
 // What bounds it.  One step per launch is bound by memory traffic, which T
 // steps per pass over the populations divide by almost T.  The levels between
 // live in LDS and not in a register window, so the kernel needs the registers
-// of the node update alone (binary32: 83, binary64: 110) and four wavefronts
-// share a SIMD: a lone wavefront issues one instruction every 6 to 9 cycles on
+// of the node update alone (binary32: 78 to 88, binary64: 102 to 118) and four
+// wavefronts share a SIMD: a lone wavefront issues one instruction every 6 to 9 cycles on
 // this chip, where several together issue one every 3 (binary32) to 5
 // (binary64).  A marching wavefront with the window in registers ran at two
 // (binary32) and one (binary64) per SIMD.  With two steps the memory still
